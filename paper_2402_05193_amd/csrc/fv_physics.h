@@ -196,14 +196,6 @@ __device__ __forceinline__ void prim_to_cons(const Material<Real>& mat, const Re
 }
 
 // ---------------------------------------------------------------- WENO5-Z
-// Both one-sided WENO5-Z values of cell i from v_{i-2..i+2} = a,b,c,d,e:
-//   vm = v^-_{i+1/2} (left-biased, stencils {i-2..i}, {i-1..i+1}, {i..i+2},
-//        linear weights 1/10, 6/10, 3/10),
-//   vp = v^+_{i-1/2} (the mirror image: same smoothness indicators in
-//        reverse order).
-// Weights alpha_k = d_k (1 + tau / (beta_k + eps)) with tau = |beta0 - beta2|
-// (WENO-Z, exponent 1).  The 1/(beta_k + eps) and the factors
-// g_k = 1 + tau/(beta_k + eps) are computed once for both sides.
 // WENO-Z weights (q = 1) in FP32 for data of any magnitude: g_k = 1 + tau / e_k
 // (e_k = beta_k + eps) overflows once tau exceeds ~1e8 with eps = 1e-30 (a jump
 // of ~2e4 in the reconstructed variable, e.g. a pressure jump in pascals).  The
@@ -213,7 +205,7 @@ __device__ __forceinline__ void prim_to_cons(const Material<Real>& mat, const Re
 // candidate when A underflows (tau / e_min beyond the FP32 range; e_min C stays
 // near e_min >= eps).  Weights of order one also keep the weighted sums of
 // small-valued fields out of the denormal range, which weights scaled by e_min
-// do not.  FP64 (eps = 1e-40) keeps the plain form.
+// do not.  FP64 (eps = 1e-40) scales the weights by e_0 e_1 e_2 instead.
 __device__ __forceinline__ void weno_z_scaled(float tau, float e0, float e1, float e2, float& s0, float& s1,
                                               float& s2)
 {
@@ -225,98 +217,91 @@ __device__ __forceinline__ void weno_z_scaled(float tau, float e0, float e1, flo
     s2 = fmaf(Cm, rcp(e2), A);
 }
 
+// WENO5-Z in differences.  With d1 .. d4 the first differences of v_{i-2} .. v_{i+2}
+// and t0, t1, t2 their differences (the second differences of the three candidate
+// stencils), the smoothness indicators are
+//   beta_0 = 13/12 t0^2 + (d2 + t0/2)^2,  beta_1 = 13/12 t1^2 + ((d2 + d3)/2)^2,
+//   beta_2 = 13/12 t2^2 + (d3 - t2/2)^2
+// and the value at the + face is v_i plus the weighted candidate increments
+//   (5 d2 - 2 d1)/6, (d2 + 2 d3)/6, (4 d3 - d4)/6  with weights (1, 6, 3) g_k
+// (linear weights 1/10, 6/10, 3/10; g_k = 1 + tau/(beta_k + eps), tau = |beta_0 -
+// beta_2|, WENO-Z with exponent 1); the - face is the mirror image (differences
+// negated and reversed, g reversed).  In FP64 the g_k are scaled by the product of
+// the three indicators, e_0 e_1 e_2 + tau e_1 e_2 etc. (e_k = beta_k + eps): the
+// weights only count relative to each other, so no reciprocal is taken for them.
+// Rounding errors scale with the data's variation, and a uniform stencil returns
+// v_i exactly.
+//
+// 13/12 t^2 + eps of one candidate stencil's second difference
+template <typename Real>
+__device__ __forceinline__ Real weno5z_curvature(Real t, Real eps)
+{
+    return fma(Real(13.0 / 12.0) * t, t, eps);
+}
+
+// the weights of a cell from d2, d3, the second differences t0, t2 and the curvature
+// terms c_k = weno5z_curvature(t_k) (shared by neighbouring cells)
+template <typename Real>
+__device__ __forceinline__ void weno5z_weights(Real d2, Real d3, Real t0, Real t2, Real c0, Real c1, Real c2, Real& g0,
+                                               Real& g1, Real& g2)
+{
+    const Real h0 = fma(Real(0.5), t0, d2), h2 = fma(Real(-0.5), t2, d3), x = d2 + d3;
+    const Real e0 = fma(h0, h0, c0), e1 = fma(Real(0.25) * x, x, c1), e2 = fma(h2, h2, c2);
+    const Real tau = fabs(e0 - e2);
+    if constexpr (sizeof(Real) == 8) {
+        const Real p01 = e0 * e1, p02 = e0 * e2, p12 = e1 * e2, p = p01 * e2;
+        g0 = fma(tau, p12, p);
+        g1 = fma(tau, p02, p);
+        g2 = fma(tau, p01, p);
+    } else {
+        weno_z_scaled(tau, e0, e1, e2, g0, g1, g2);
+    }
+}
+
+// the + face value of a cell of value v from its weights and differences
+template <typename Real>
+__device__ __forceinline__ Real weno5z_value(Real v, Real d1, Real d2, Real d3, Real d4, Real g0, Real g1, Real g2)
+{
+    const Real y = Real(2) * d3, a0 = g0 * Real(1.0 / 3.0);
+    const Real n = fma(a0, fma(Real(2.5), d2, -d1), fma(g1, y + d2, g2 * fma(Real(-0.5), d4, y)));
+    return fma(n, rcp(fma(Real(3), g2, fma(Real(6), g1, g0))), v);
+}
+
+// Both one-sided WENO5-Z values of cell i from v_{i-2..i+2} = a,b,c,d,e:
+//   vm = v^-_{i+1/2} (left-biased, stencils {i-2..i}, {i-1..i+1}, {i..i+2}),
+//   vp = v^+_{i-1/2} (the mirror image: same smoothness indicators in
+//        reverse order).
 template <typename Real>
 __device__ __forceinline__ void weno5z_pair(Real a, Real b, Real c, Real d, Real e, Real eps, Real& vm,
                                             Real& vp)
 {
-    const Real k13 = Real(13.0 / 12.0), q = Real(0.25);
-    const Real t0 = a - Real(2) * b + c;
-    const Real s0 = a - Real(4) * b + Real(3) * c;
-    const Real t1 = b - Real(2) * c + d;
-    const Real s1 = b - d;
-    const Real t2 = c - Real(2) * d + e;
-    const Real s2 = Real(3) * c - Real(4) * d + e;
-    const Real b0 = k13 * t0 * t0 + q * s0 * s0;
-    const Real b1 = k13 * t1 * t1 + q * s1 * s1;
-    const Real b2 = k13 * t2 * t2 + q * s2 * s2;
-    const Real tau = fabs(b0 - b2);
-    const Real e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps;
+    const Real d1 = b - a, d2 = c - b, d3 = d - c, d4 = e - d;
+    const Real t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
     Real g0, g1, g2;
-    if constexpr (sizeof(Real) == 8) {
-        // one reciprocal for the three indicators: 1/e_k from 1/(e0 e1 e2)
-        const Real p01 = e0 * e1;
-        const Real R = rcp(p01 * e2);
-        const Real t = e2 * R;
-        const Real r2 = p01 * R;
-        const Real r0 = e1 * t;
-        const Real r1 = e0 * t;
-        g0 = fma(tau, r0, Real(1));
-        g1 = fma(tau, r1, Real(1));
-        g2 = fma(tau, r2, Real(1));
-    } else {
-        weno_z_scaled(tau, e0, e1, e2, g0, g1, g2);
-    }
-    // candidate values (times 6)
-    const Real p0 = Real(2) * a - Real(7) * b + Real(11) * c;
-    const Real p1 = -b + Real(5) * c + Real(2) * d;
-    const Real p2 = Real(2) * c + Real(5) * d - e;
-    const Real u0 = Real(2) * e - Real(7) * d + Real(11) * c;
-    const Real u1 = -d + Real(5) * c + Real(2) * b;
-    const Real u2 = Real(2) * c + Real(5) * b - a;
-    // alpha scaled by 10: (1, 6, 3) g for vm and (3, 6, 1) g reversed for vp
-    const Real m1 = Real(6) * g1, m2 = Real(3) * g2, n2 = Real(3) * g0;
-    const Real dm = Real(6) * (g0 + m1 + m2);
-    const Real dp = Real(6) * (g2 + m1 + n2);
-    Real idm, idp;
-    if constexpr (sizeof(Real) == 8) {
-        const Real R = rcp(dm * dp);
-        idm = dp * R;
-        idp = dm * R;
-    } else {
-        idm = rcp(dm);
-        idp = rcp(dp);
-    }
-    vm = (g0 * p0 + m1 * p1 + m2 * p2) * idm;
-    vp = (g2 * u0 + m1 * u1 + n2 * u2) * idp;
+    weno5z_weights(d2, d3, t0, t2, weno5z_curvature(t0, eps), weno5z_curvature(t1, eps), weno5z_curvature(t2, eps), g0,
+                   g1, g2);
+    vm = weno5z_value(c, d1, d2, d3, d4, g0, g1, g2);
+    vp = weno5z_value(c, -d4, -d3, -d2, -d1, g2, g1, g0);
 }
 
-// One-sided WENO5-Z value v^-_{i+1/2} from v_{i-2..i+2} = a,b,c,d,e (the v^+
-// value of a face is the same function of the mirrored stencil).
+// Both states of the face between cells i and i+1 from v_{i-2..i+3} = v[0..5]: L is the
+// left-biased value of cell i, R the mirrored one of cell i+1.
 template <typename Real>
-__device__ __forceinline__ Real weno5z_one(Real a, Real b, Real c, Real d, Real e, Real eps)
+__device__ __forceinline__ void weno5z_face(const Real* v, Real eps, Real& L, Real& R)
 {
-    const Real k13 = Real(13.0 / 12.0), q = Real(0.25);
-    const Real t0 = a - Real(2) * b + c;
-    const Real s0 = a - Real(4) * b + Real(3) * c;
-    const Real t1 = b - Real(2) * c + d;
-    const Real s1 = b - d;
-    const Real t2 = c - Real(2) * d + e;
-    const Real s2 = Real(3) * c - Real(4) * d + e;
-    const Real b0 = k13 * t0 * t0 + q * s0 * s0;
-    const Real b1 = k13 * t1 * t1 + q * s1 * s1;
-    const Real b2 = k13 * t2 * t2 + q * s2 * s2;
-    const Real tau = fabs(b0 - b2);
-    const Real e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps;
-    Real g0, g1, g2;
-    if constexpr (sizeof(Real) == 8) {
-        const Real p01 = e0 * e1;
-        const Real R = rcp(p01 * e2);
-        const Real t = e2 * R;
-        const Real r2 = p01 * R;
-        const Real r0 = e1 * t;
-        const Real r1 = e0 * t;
-        g0 = fma(tau, r0, Real(1));
-        g1 = fma(tau, r1, Real(1));
-        g2 = fma(tau, r2, Real(1));
-    } else {
-        weno_z_scaled(tau, e0, e1, e2, g0, g1, g2);
+    Real d[5], t[4], c[4];
+#pragma unroll
+    for (int k = 0; k < 5; k++) d[k] = v[k + 1] - v[k];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        t[k] = d[k + 1] - d[k];
+        c[k] = weno5z_curvature(t[k], eps);
     }
-    const Real m1 = Real(6) * g1;
-    const Real m2 = Real(3) * g2;
-    const Real p0 = Real(2) * a - Real(7) * b + Real(11) * c;
-    const Real p1 = -b + Real(5) * c + Real(2) * d;
-    const Real p2 = Real(2) * c + Real(5) * d - e;
-    return (g0 * p0 + m1 * p1 + m2 * p2) * rcp(Real(6) * (g0 + m1 + m2));
+    Real g0, g1, g2;
+    weno5z_weights(d[1], d[2], t[0], t[2], c[0], c[1], c[2], g0, g1, g2);
+    L = weno5z_value(v[2], d[0], d[1], d[2], d[3], g0, g1, g2);
+    weno5z_weights(d[2], d[3], t[1], t[3], c[1], c[2], c[3], g0, g1, g2);
+    R = weno5z_value(v[3], -d[4], -d[3], -d[2], -d[1], g2, g1, g0);
 }
 
 // ---------------------------------------------------------------- TENO6-A
@@ -477,8 +462,7 @@ __device__ __forceinline__ void char_face_states(const Material<Real>& mat, Sten
         if constexpr (TENO) {
             teno6a_pair(q[0], q[1], q[2], q[3], q[4], q[5], eps, L, R);
         } else {
-            L = weno5z_one(q[0], q[1], q[2], q[3], q[4], eps);
-            R = weno5z_one(q[5], q[4], q[3], q[2], q[1], eps);
+            weno5z_face(q, eps, L, R);
         }
     };
     Real amL, amR, apL, apR;

@@ -204,9 +204,6 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     const int tid = threadIdx.x;
     const bool has_cell = tid < NCELL;  // threads beyond the tile only take x/y tasks
     const int tx = tid % BX, ty = has_cell ? tid / BX : 0;
-    // task lists have a few tasks more than threads; the wave that takes the
-    // remainder rotates with the workgroup so co-resident groups spread it over SIMDs
-    const int rt = (tid + 64 * (bid & 3)) % NT;
     int b = bid;
     // blocks of one tile column are consecutive; consecutive tiles share an XCD's L2
     const int chunk = b % a.nchunks;
@@ -217,7 +214,6 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     const int z0 = chunk * a.zchunk;
     const int z1 = min(z0 + a.zchunk, a.nz);
     const int gx = x0 + tx, gy = y0 + ty;
-    const bool own_valid = has_cell && gx < a.nx && gy < a.ny;
     // the tile and its 3-cell x/y halo lie inside the domain: no boundary mapping in x, y
     const bool interior_xy = x0 >= 3 && x0 + BX + 3 <= a.nx && y0 >= 3 && y0 + BY + 3 <= a.ny;
 
@@ -326,6 +322,21 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     }
 
     for (int s = s_begin; s <= z1 + 1; s++) {
+        // the thread's indices formed anew in every step from a copy that the compiler does
+        // not see through: otherwise it computes the index arithmetic of every phase once
+        // and holds it in registers across the plane loop.  NS FP64 56 -> 0 spilled VGPRs,
+        // FP32 16 -> 0 (168 -> 139 VGPRs), five-equation FP64 84 -> 70; per stage NS 256^3
+        // 2.40 -> 2.06 ms, five-equation THINC FP32 192x96x96 0.33 -> 0.30.  The TENO6-A
+        // kernels measured 1-2 % slower with it.
+        int tid = threadIdx.x;
+        if constexpr (!TENO) asm volatile("" : "+v"(tid));
+        const bool has_cell = tid < NCELL;
+        const int tx = tid % BX, ty = has_cell ? tid / BX : 0;
+        // task lists have a few tasks more than threads; the wave that takes the
+        // remainder rotates with the workgroup so co-resident groups spread it over SIMDs
+        const int rt = (tid + 64 * (bid & 3)) % NT;
+        const int gx = x0 + tx, gy = y0 + ty;
+        const bool own_valid = has_cell && gx < a.nx && gy < a.ny;
         // own column, plane s+2.  Without viscous fluxes it is not read before the next
         // step: the five-equation and Euler kernels load it after the z work and convert it
         // at the end of the step (OWN_AFTER_Z), so that neither the loaded nor the converted
