@@ -284,6 +284,29 @@ __device__ __forceinline__ void weno5z_pair(Real a, Real b, Real c, Real d, Real
     vp = weno5z_value(c, -d4, -d3, -d2, -d1, g2, g1, g0);
 }
 
+// The same for two neighbouring cells i, i+1 from v_{i-2..i+3} = v[0..5] (the same
+// arithmetic, bit for bit): they share a difference, two second differences and their
+// curvature terms, and six loads serve where two single cells take ten.
+template <typename Real>
+__device__ __forceinline__ void weno5z_two(const Real* v, Real eps, Real* vm, Real* vp)
+{
+    Real d[5], t[4], c[4];
+#pragma unroll
+    for (int k = 0; k < 5; k++) d[k] = v[k + 1] - v[k];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        t[k] = d[k + 1] - d[k];
+        c[k] = weno5z_curvature(t[k], eps);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        Real g0, g1, g2;
+        weno5z_weights(d[q + 1], d[q + 2], t[q], t[q + 2], c[q], c[q + 1], c[q + 2], g0, g1, g2);
+        vm[q] = weno5z_value(v[q + 2], d[q], d[q + 1], d[q + 2], d[q + 3], g0, g1, g2);
+        vp[q] = weno5z_value(v[q + 2], -d[q + 3], -d[q + 2], -d[q + 1], -d[q], g2, g1, g0);
+    }
+}
+
 // Both states of the face between cells i and i+1 from v_{i-2..i+3} = v[0..5]: L is the
 // left-biased value of cell i, R the mirrored one of cell i+1.
 template <typename Real>
@@ -784,11 +807,11 @@ __device__ __forceinline__ void viscous_flux_from_gradients(const Real* dn, cons
 
 // The same flux reading its inputs from LDS one quantity at a time.
 //  vel: &u at the first of the four cells (u, v, w are `fstride` apart),
-//  temp: &T at the first cell; consecutive cells are `cstride` apart.
+//  temp: &T at the first cell; consecutive cells are `cstride` (T: `tstride`) apart.
 //  t1n, t2n, t1t1, t2t2: d u_n/d x_t1, d u_n/d x_t2, d u_t1/d x_t1, d u_t2/d x_t2
 //  at the first cell, consecutive cells `dstride` apart.
 template <typename Real, int DIR>
-__device__ __forceinline__ void viscous_flux_lds(const Real* vel, const Real* temp, int cstride, int fstride,
+__device__ __forceinline__ void viscous_flux_lds(const Real* vel, const Real* temp, int cstride, int tstride, int fstride,
                                                  const Real* t1n, const Real* t2n, const Real* t1t1,
                                                  const Real* t2t2, int dstride, Real mu, Real kappa, Real inv24h,
                                                  Real* Fd)
@@ -799,7 +822,8 @@ __device__ __forceinline__ void viscous_flux_lds(const Real* vel, const Real* te
 #pragma unroll
     for (int c = 0; c < 4; c++) {
         const Real* q = c < 3 ? vel + c * fstride : temp;
-        const Real a = q[0], b = q[cstride], cc = q[2 * cstride], d = q[3 * cstride];
+        const int st = c < 3 ? cstride : tstride;
+        const Real a = q[0], b = q[st], cc = q[2 * st], d = q[3 * st];
         dn[c] = dface(a, b, cc, d, inv24h);
         if (c < 3) vf[c] = ifc(a, b, cc, d);
     }

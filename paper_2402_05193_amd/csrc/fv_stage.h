@@ -120,6 +120,31 @@ __device__ __forceinline__ double inverse_dt(const StageArgs<Real>& a, const Rea
     return d >= 0.0 ? d : __longlong_as_double(0x7ff0000000000000ll);  // NaN -> +inf
 }
 
+// Calls item(m, a, b) for every component m < NC and every a < NA, b < NB of a task list
+// spread over NT threads (list position (m NA + a) NB + b, thread t first takes position
+// t), b fastest across the lanes.  The position is advanced by NT without divisions
+// (b from a 24-bit multiply); the loop stays rolled for its registers.
+template <int NB, int NA, int NC, int NT, typename Item>
+__device__ __forceinline__ void pair_items(int t, Item item)
+{
+    constexpr int N = NA * NB;                 // positions per component
+    constexpr int SM = NT / N, ST = NT % N;    // one stride of NT
+    constexpr unsigned SH = 16, MUL = ((1u << SH) + NB - 1) / NB;
+    static_assert(N <= (1 << 12) && MUL * NB - (1u << SH) < (1u << SH) / N, "exact quotient for every position");
+    int m = t / N, r = t - m * N;
+#pragma unroll 1
+    while (m < NC) {
+        const int a = (int)(__umul24((unsigned)r, MUL) >> SH);
+        item(m, a, r - a * NB);
+        m += SM;
+        r += ST;
+        if (r >= N) {
+            r -= N;
+            m++;
+        }
+    }
+}
+
 // LDS geometry of one tile of BX x BY cells worked on by NTH threads
 // (NTH >= BX * BY; the x/y task lists are sized to fit NTH in one round)
 template <typename Real, int MODEL, int BX, int BY, int NTH, bool VISC_ = (MODEL == NS), bool THINC_ = false>
@@ -129,15 +154,21 @@ struct Tile {
     static constexpr bool THINC = THINC_;  // interface capturing (five-equation model)
     static constexpr int NT = NTH;
     static constexpr int NCELL = BX * BY;
-    // primitives of the LDS plane, plus T = p/rho (viscous) or the smoothed volume
-    // fraction psi of the interface normal (THINC)
-    static constexpr int NW = NC + ((VISC || THINC) ? 1 : 0);
     static constexpr int PX = BX + 6, PY = BY + 6;  // plane with 3-cell halo
+    static constexpr int WP_SIZE = NC * PY * PX;    // primitives of the LDS plane
+    // T = p/rho (viscous) or the smoothed volume fraction psi of the interface normal
+    // (THINC) on the plane with a 2-cell halo, as far out as either is read
+    static constexpr int QX = BX + 4, QY = BY + 4;
+    static constexpr int WQ_SIZE = (VISC || THINC) ? QX * QY : 0;
     static constexpr int NFX = (BX + 1) * BY, NFY = BX * (BY + 1);
-    static constexpr int NFMAX = NFX > NFY ? NFX : NFY;
-    static constexpr int WP_SIZE = NW * PY * PX;
-    static constexpr int FB_SIZE = 2 * NC * NFMAX;       // face states (left, right), fluxes in place
-    static constexpr int UH_SIZE = MODEL == DIM ? NFMAX : 0;
+    // face states (left, right), fluxes in place.  x: row j holds BX + 2 entries, the left
+    // state of face f at f and the right one at f + 1, so that cell i's two values both go
+    // to entry i + 1 (entry BX + 1 of the left and 0 of the right states are never read);
+    // y: BY + 2 rows of BX, rows in the place of entries
+    static constexpr int FRX = BX + 2;
+    static constexpr int FSZ = FRX * BY > BX * (BY + 2) ? FRX * BY : BX * (BY + 2);
+    static constexpr int FB_SIZE = 2 * NC * FSZ;
+    static constexpr int UH_SIZE = MODEL == DIM ? FSZ : 0;
     static constexpr int RX = (BX + 4) * BY, RY = BX * (BY + 4);  // viscous cell regions
     static constexpr int DZ_SIZE = VISC ? 2 * RX + 2 * RY : 0;    // d/dz of (u,w) on RX, (v,w) on RY
     static constexpr int DT_SIZE = VISC ? 2 * (RX > RY ? RX : RY) : 0;  // in-plane tangential d/dx_t
@@ -159,7 +190,7 @@ struct Tile {
     static constexpr int ACC_SIZE = ACC_LDS ? 2 * NC * NCELL : (ACC_HALF ? NC * NCELL : 0);
     static constexpr size_t bytes()
     {
-        return sizeof(Real) * (size_t)(WP_SIZE + FB_SIZE + UH_SIZE + DZ_SIZE + DT_SIZE + ACC_SIZE + AZ_SIZE + PSQ_SIZE);
+        return sizeof(Real) * (size_t)(WP_SIZE + WQ_SIZE + FB_SIZE + UH_SIZE + DZ_SIZE + DT_SIZE + ACC_SIZE + AZ_SIZE + PSQ_SIZE);
     }
 };
 
@@ -179,6 +210,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     constexpr int NT = NTH;
     constexpr int NCELL = BX * BY;
     constexpr int PLANE = PY * PX;
+    constexpr int FSZ = TL::FSZ, FRX = TL::FRX;
     static_assert(NT >= NCELL && NT % 64 == 0, "threads must cover the tile");
     // POS: 0 limiters off, 1 on, 2 on and every face's decisions written to a.flags
     // (bit 0: interpolation limiter on the left state, bit 1: on the right state,
@@ -187,7 +219,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     constexpr bool REC_FLAGS = POS == 2;
 
     Real* Wp = reinterpret_cast<Real*>(smem_raw);
-    Real* FB = Wp + TL::WP_SIZE;
+    Real* Wq = Wp + TL::WP_SIZE;   // [QY][QX]  T or psi
+    Real* FB = Wq + TL::WQ_SIZE;
     Real* UHB = FB + TL::FB_SIZE;
     Real* DZX = UHB + TL::UH_SIZE;  // [2][BY][BX+4]   (u, w) d/dz, x-face region
     Real* DZY = DZX + 2 * TL::RX;   // [2][BY+4][BX]   (v, w) d/dz, y-face region
@@ -218,6 +251,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     const bool interior_xy = x0 >= 3 && x0 + BX + 3 <= a.nx && y0 >= 3 && y0 + BY + 3 <= a.ny;
 
     auto wp = [&](int f, int i, int j) -> Real& { return Wp[f * PLANE + (j + 3) * PX + (i + 3)]; };
+    constexpr int QX = TL::QX;
+    auto wq = [&](int i, int j) -> Real& { return Wq[(j + 2) * QX + (i + 2)]; };
 
     // primitive state of an arbitrary (possibly outside) cell
     auto load_w = [&](int gi, int gj, int gk, Real* w) {
@@ -225,12 +260,14 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         load_cell<Real>(a, a.Uk, gi, gj, gk, u, NC, V, interior_xy);
         cons_to_prim<Real, MODEL>(mat, u, w);
     };
-    auto stage_w = [&](int i, int j, const Real* w, Real psi, bool with_psi = true) {
+    auto stage_w = [&](int i, int j, const Real* w, Real psi, bool with_q = true) {
 #pragma unroll
         for (int f = 0; f < NC; f++) wp(f, i, j) = w[f];
-        if constexpr (VISC) wp(NC, i, j) = w[P] * rcp(w[0]);  // T = p / rho
+        if constexpr (VISC) {
+            if (with_q) wq(i, j) = w[P] * rcp(w[0]);  // T = p / rho
+        }
         if constexpr (THINC) {
-            if (with_psi) wp(NC, i, j) = psi;
+            if (with_q) wq(i, j) = psi;
         }
     };
 
@@ -394,7 +431,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // THINC: psi is read on the tile, the 1-cell ring (staged by the ring's
             // threads with PSI_CARRY) and the second ring's arms; a halo thread evaluates
             // it only there
-            bool hpsi_needed = true;
+            bool hq_needed = true;
             // FP64 five-equation WENO5-Z kernels: the halo index passes through an empty asm
             // here, so that the halo loads are issued in this step; the compiler otherwise
             // moved them to the end of the previous step, where their values, live across
@@ -412,13 +449,13 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     hj = h / 6;
                     const int k = h % 6;
                     hi = k < 3 ? k - 3 : BX + k - 3;
-                    if constexpr (PSI_CARRY) hpsi_needed = k == 1 || k == 4;
+                    hq_needed = PSI_CARRY ? k == 1 || k == 4 : k != 0 && k != 5;
                 } else if (h < 6 * BY + 6 * BX) {
                     const int hh = h - 6 * BY;
                     hi = hh % BX;
                     const int k = hh / BX;
                     hj = k < 3 ? k - 3 : BY + k - 3;
-                    if constexpr (PSI_CARRY) hpsi_needed = k == 1 || k == 4;
+                    hq_needed = PSI_CARRY ? k == 1 || k == 4 : k != 0 && k != 5;
                 } else if constexpr (VISC) {
                     const int hh = h - 6 * BY - 6 * BX;  // 2-deep corners (viscous cross terms)
                     const int ci = hh & 3, cj = hh >> 2;
@@ -428,7 +465,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     const int hh = h - 6 * BY - 6 * BX;  // 1-deep corners (THINC gradient)
                     hi = (hh & 1) ? BX : -1;
                     hj = (hh & 2) ? BY : -1;
-                    if constexpr (PSI_CARRY) hpsi_needed = false;  // a ring cell
+                    if constexpr (PSI_CARRY) hq_needed = false;  // a ring cell
                 }
                 hrefl = load_cell_raw<Real>(a, a.Uk, x0 + hi, y0 + hj, s, hu, NC, interior_xy);
             }
@@ -525,8 +562,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                         apply_reflections(hu, V, hrefl);
                         cons_to_prim<Real, MODEL>(mat, hu, w);
                         Real hpsi = 0;
-                        if (hpsi_needed) hpsi = thinc_psi(w[6]);
-                        stage_w(hi, hj, w, hpsi, hpsi_needed);
+                        if (hq_needed) hpsi = thinc_psi(w[6]);
+                        stage_w(hi, hj, w, hpsi, hq_needed);
                     }
                     halo_done = true;
                 }
@@ -548,7 +585,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                         const Real p0 = PSQ[(s & 1) * TL::NRING + rh];
                         const Real pp = thinc_psi(ring_ap);
                         AZ[(cr_j + 1) * (BX + 2) + cr_i + 1] = (pp - pm) * hz;
-                        wp(NC, cr_i, cr_j) = p0;
+                        wq(cr_i, cr_j) = p0;
                         PSQ[((s + 1) & 1) * TL::NRING + rh] = pp;  // the slot of plane s-1
                     }
                 } else if (NT - 1 - tid < TL::NRING) {
@@ -562,9 +599,9 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     cons_to_prim<Real, MODEL>(mat, hu, w);
                     Real hpsi = 0;
                     if constexpr (THINC) {
-                        if (hpsi_needed) hpsi = thinc_psi(w[6]);
+                        if (hq_needed) hpsi = thinc_psi(w[6]);
                     }
-                    stage_w(hi, hj, w, hpsi, hpsi_needed);
+                    stage_w(hi, hj, w, hpsi, hq_needed);
                 }
             }
             if constexpr (VISC) {
@@ -613,8 +650,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             }
             if (THINC && has_cell) {
                 // in-plane gradient of psi of the own column (THINC at the z faces)
-                Anew[0] = (wp(NC, tx + 1, ty) - wp(NC, tx - 1, ty)) * (Real(0.5) * idx);
-                Anew[1] = (wp(NC, tx, ty + 1) - wp(NC, tx, ty - 1)) * (Real(0.5) * idy);
+                Anew[0] = (wq(tx + 1, ty) - wq(tx - 1, ty)) * (Real(0.5) * idx);
+                Anew[1] = (wq(tx, ty + 1) - wq(tx, ty - 1)) * (Real(0.5) * idy);
             }
         } else if constexpr (!OWN_AFTER_Z) {
             convert_own();
@@ -769,14 +806,14 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // remainder wave priority 2.  NS 256^3 2.260 -> 2.18 ms per stage, five-equation
             // 256x128x128 0.949 -> 0.914 ms, Euler equal; FP32 (three workgroups per CU)
             // measured 0.4-2 % slower with it and keeps the default priority.
-            constexpr int P1_ITEMS = CHARV ? TL::NFX : (TENO ? NC * TL::NFX : NC * (BX + 2) * BY);
-            constexpr int P4_ITEMS = CHARV ? TL::NFY : (TENO ? NC * TL::NFY : NC * BX * (BY + 2));
+            constexpr int P1_ITEMS = CHARV ? TL::NFX : (TENO ? NC * TL::NFX : NC * (BX + 2) * BY / 2);
+            constexpr int P4_ITEMS = CHARV ? TL::NFY : (TENO ? NC * TL::NFY : NC * BX * (BY + 2) / 2);
             const bool prio_p1 = sizeof(Real) == 8 && (rt >> 6) < ((P1_ITEMS % NT) + 63) / 64;
             const bool prio_p4 = sizeof(Real) == 8 && (rt >> 6) < ((P4_ITEMS % NT) + 63) / 64;
             // ---- P1: x reconstructions (cells -1 .. BX of each row) [+ d/dy on the x region]
             if (prio_p1) __builtin_amdgcn_s_setprio(1);
             Real* FL = FB;
-            Real* FR = FB + NC * TL::NFX;
+            Real* FR = FB + NC * TL::FSZ;
             if constexpr (CHARV) {
                 // one task per x face: characteristic reconstruction of both face states
                 for (int t = rt; t < TL::NFX; t += NT) {
@@ -786,8 +823,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                                                            wl, wr);
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
-                        FL[m * TL::NFX + t] = wl[m];
-                        FR[m * TL::NFX + t] = wr[m];
+                        FL[m * FSZ + j * FRX + f] = wl[m];
+                        FR[m * FSZ + j * FRX + f + 1] = wr[m];
                     }
                 }
             } else if constexpr (TENO) {
@@ -796,22 +833,22 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     const int m = it / TL::NFX, t = it - m * TL::NFX;
                     const int j = t / (BX + 1), f = t - j * (BX + 1);
                     const Real* c = &wp(m, f - 3, j);
-                    teno6a_pair(c[0], c[1], c[2], c[3], c[4], c[5], weps, FL[it], FR[it]);
+                    const int e = m * FSZ + j * FRX + f;
+                    teno6a_pair(c[0], c[1], c[2], c[3], c[4], c[5], weps, FL[e], FR[e + 1]);
                 }
             } else {
-                // one item = one component of one cell; consecutive lanes take consecutive cells
-                constexpr int NTX = (BX + 2) * BY;
-                auto item = [&](int it) {
-                    const int m = it / NTX, t = it - m * NTX;
-                    const int j = t / (BX + 2), i = t - j * (BX + 2) - 1;
-                    const Real* c = &wp(m, i, j);
-                    Real vm, vp;
-                    weno5z_pair(c[-2], c[-1], c[0], c[1], c[2], weps, vm, vp);
-                    if (i < BX) FL[m * TL::NFX + j * (BX + 1) + i + 1] = vm;
-                    if (i >= 0) FR[m * TL::NFX + j * (BX + 1) + i] = vp;
-                };
-#pragma unroll 1
-                for (int it = rt; it < NC * NTX; it += NT) item(it);
+                // one item = one component of two neighbouring cells 2q-1, 2q of a row
+                pair_items<(BX + 2) / 2, BY, NC, NT>(rt, [&](int m, int j, int q) {
+                    const Real* c = &Wp[m * PLANE + (j + 3) * PX + 2 * q];
+                    const Real v[6] = {c[0], c[1], c[2], c[3], c[4], c[5]};
+                    Real vm[2], vp[2];
+                    weno5z_two(v, weps, vm, vp);
+                    const int e = m * FSZ + j * FRX + 2 * q;
+                    FL[e] = vm[0];
+                    FL[e + 1] = vm[1];
+                    FR[e] = vp[0];
+                    FR[e + 1] = vp[1];
+                });
             }
             if constexpr (VISC) {
                 // d/dy of u (c = 0) and v (c = 1) on the x-face region
@@ -830,22 +867,23 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             if (prio_tail) __builtin_amdgcn_s_setprio(2);
             for (int t = rt; t < TL::NFX; t += NT) {
                 const int j = t / (BX + 1), f = t % (BX + 1);
+                const int e = j * FRX + f;
                 Real wl[NC], wr[NC], F[NC], uh;
 #pragma unroll
                 for (int m = 0; m < NC; m++) {
-                    wl[m] = FL[m * TL::NFX + t];
-                    wr[m] = FR[m * TL::NFX + t];
+                    wl[m] = FL[m * FSZ + e];
+                    wr[m] = FR[m * FSZ + e + 1];
                 }
                 if constexpr (THINC) {
                     // interface cells f-1 (its +x face) and f (its -x face)
                     const Real hx = Real(0.5) * idx, hy = Real(0.5) * idy;
                     const Real am = wp(6, f - 2, j), a0 = wp(6, f - 1, j), a1 = wp(6, f, j), ap = wp(6, f + 1, j);
-                    Real af, gx = (wp(NC, f, j) - wp(NC, f - 2, j)) * hx;
-                    Real gy = (wp(NC, f - 1, j + 1) - wp(NC, f - 1, j - 1)) * hy, gz = AZ[(j + 1) * (BX + 2) + f];
+                    Real af, gx = (wq(f, j) - wq(f - 2, j)) * hx;
+                    Real gy = (wq(f - 1, j + 1) - wq(f - 1, j - 1)) * hy, gz = AZ[(j + 1) * (BX + 2) + f];
                     if (thinc_face(am, a0, a1, gx, gx * gx + gy * gy + gz * gz, 1, af))
                         thinc_state(af, wp(0, f - 1, j), wp(1, f - 1, j), a0, wl);
-                    gx = (wp(NC, f + 1, j) - wp(NC, f - 1, j)) * hx;
-                    gy = (wp(NC, f, j + 1) - wp(NC, f, j - 1)) * hy;
+                    gx = (wq(f + 1, j) - wq(f - 1, j)) * hx;
+                    gy = (wq(f, j + 1) - wq(f, j - 1)) * hy;
                     gz = AZ[(j + 1) * (BX + 2) + f + 1];
                     if (thinc_face(a0, a1, ap, gx, gx * gx + gy * gy + gz * gz, 0, af))
                         thinc_state(af, wp(0, f, j), wp(1, f, j), a1, wr);
@@ -882,11 +920,11 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     Real Fd[4];
                     Real muf = a.mu, kf = a.kappa;
                     if constexpr (VLAW) {
-                        const Real* th = &wp(NC, f - 2, j);
+                        const Real* th = &wq(f - 2, j);
                         muf = visc_mu(a.vl, ifc(th[0], th[1], th[2], th[3]));
                         kf = muf * a.vl.kfac;
                     }
-                    viscous_flux_lds<Real, 0>(&wp(V, f - 2, j), &wp(NC, f - 2, j), 1, PLANE, DT + r0, DZX + r0,
+                    viscous_flux_lds<Real, 0>(&wp(V, f - 2, j), &wq(f - 2, j), 1, 1, PLANE, DT + r0, DZX + r0,
                                               DT + TL::RX + r0, DZX + TL::RX + r0, 1, muf, kf, a.inv24dx, Fd);
                     F[V] -= Fd[0];
                     F[V + 1] -= Fd[1];
@@ -894,17 +932,17 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     F[P] -= Fd[3];
                 }
 #pragma unroll
-                for (int m = 0; m < NC; m++) FL[m * TL::NFX + t] = F[m];
-                if constexpr (MODEL == DIM) UHB[t] = uh;
+                for (int m = 0; m < NC; m++) FL[m * FSZ + e] = F[m];
+                if constexpr (MODEL == DIM) UHB[e] = uh;
             }
             if (prio_tail) __builtin_amdgcn_s_setprio(0);
             __syncthreads();
             // ---- P3: x divergence of the own cell
             if (has_cell) {
-                const int fl = ty * (BX + 1) + tx;
+                const int fl = ty * FRX + tx;
 #pragma unroll
                 for (int m = 0; m < NC; m++) {
-                    const Real v = -(FL[m * TL::NFX + fl + 1] - FL[m * TL::NFX + fl]) * idx;
+                    const Real v = -(FL[m * FSZ + fl + 1] - FL[m * FSZ + fl]) * idx;
                     if constexpr (ACC_LDS) slot[m * NCELL] = v;
                     else accC[m] = v;
                 }
@@ -914,7 +952,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // ---- P4: y reconstructions (rows -1 .. BY of each column) [+ d/dx on the y region]
             if (prio_p4) __builtin_amdgcn_s_setprio(1);
             Real* GL = FB;
-            Real* GR = FB + NC * TL::NFY;
+            Real* GR = FB + NC * FSZ;
             if constexpr (CHARV) {
                 for (int t = rt; t < TL::NFY; t += NT) {
                     const int f = t / BX, i = t - f * BX;
@@ -923,8 +961,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                                                            wl, wr);
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
-                        GL[m * TL::NFY + t] = wl[m];
-                        GR[m * TL::NFY + t] = wr[m];
+                        GL[m * FSZ + t] = wl[m];
+                        GR[m * FSZ + t + BX] = wr[m];
                     }
                 }
             } else if constexpr (TENO) {
@@ -933,22 +971,22 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     const int m = it / TL::NFY, t = it - m * TL::NFY;
                     const int f = t / BX, i = t - f * BX;
                     const Real* c = &wp(m, i, f - 3);
-                    teno6a_pair(c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX], weps, GL[it], GR[it]);
+                    teno6a_pair(c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX], weps, GL[m * FSZ + t],
+                                GR[m * FSZ + t + BX]);
                 }
             } else {
-                // one item = one component of one cell; consecutive lanes take consecutive cells
-                constexpr int NTY = BX * (BY + 2);
-                auto item = [&](int it) {
-                    const int m = it / NTY, t = it - m * NTY;
-                    const int jj = t / BX, i = t - jj * BX, j = jj - 1;
-                    const Real* c = &wp(m, i, j);
-                    Real vm, vp;
-                    weno5z_pair(c[-2 * PX], c[-PX], c[0], c[PX], c[2 * PX], weps, vm, vp);
-                    if (j < BY) GL[m * TL::NFY + (j + 1) * BX + i] = vm;
-                    if (j >= 0) GR[m * TL::NFY + j * BX + i] = vp;
-                };
-#pragma unroll 1
-                for (int it = rt; it < NC * NTY; it += NT) item(it);
+                // one item = one component of two neighbouring cells 2q-1, 2q of a column
+                pair_items<BX, (BY + 2) / 2, NC, NT>(rt, [&](int m, int q, int i) {
+                    const Real* c = &Wp[m * PLANE + 2 * q * PX + i + 3];
+                    const Real v[6] = {c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX]};
+                    Real vm[2], vp[2];
+                    weno5z_two(v, weps, vm, vp);
+                    const int e = m * FSZ + 2 * q * BX + i;
+                    GL[e] = vm[0];
+                    GL[e + BX] = vm[1];
+                    GR[e] = vp[0];
+                    GR[e + BX] = vp[1];
+                });
             }
             if constexpr (VISC) {
                 // d/dx of v (c = 0) and u (c = 1) on the y-face region
@@ -969,19 +1007,19 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 Real wl[NC], wr[NC], F[NC], uh;
 #pragma unroll
                 for (int m = 0; m < NC; m++) {
-                    wl[m] = GL[m * TL::NFY + t];
-                    wr[m] = GR[m * TL::NFY + t];
+                    wl[m] = GL[m * FSZ + t];
+                    wr[m] = GR[m * FSZ + t + BX];
                 }
                 if constexpr (THINC) {
                     // interface cells of rows f-1 (its +y face) and f (its -y face)
                     const Real hx = Real(0.5) * idx, hy = Real(0.5) * idy;
                     const Real am = wp(6, i, f - 2), a0 = wp(6, i, f - 1), a1 = wp(6, i, f), ap = wp(6, i, f + 1);
-                    Real af, gy = (wp(NC, i, f) - wp(NC, i, f - 2)) * hy;
-                    Real gx = (wp(NC, i + 1, f - 1) - wp(NC, i - 1, f - 1)) * hx, gz = AZ[f * (BX + 2) + i + 1];
+                    Real af, gy = (wq(i, f) - wq(i, f - 2)) * hy;
+                    Real gx = (wq(i + 1, f - 1) - wq(i - 1, f - 1)) * hx, gz = AZ[f * (BX + 2) + i + 1];
                     if (thinc_face(am, a0, a1, gy, gx * gx + gy * gy + gz * gz, 1, af))
                         thinc_state(af, wp(0, i, f - 1), wp(1, i, f - 1), a0, wl);
-                    gy = (wp(NC, i, f + 1) - wp(NC, i, f - 1)) * hy;
-                    gx = (wp(NC, i + 1, f) - wp(NC, i - 1, f)) * hx;
+                    gy = (wq(i, f + 1) - wq(i, f - 1)) * hy;
+                    gx = (wq(i + 1, f) - wq(i - 1, f)) * hx;
                     gz = AZ[(f + 1) * (BX + 2) + i + 1];
                     if (thinc_face(a0, a1, ap, gy, gx * gx + gy * gy + gz * gz, 0, af))
                         thinc_state(af, wp(0, i, f), wp(1, i, f), a1, wr);
@@ -1018,11 +1056,11 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     Real Fd[4];
                     Real muf = a.mu, kf = a.kappa;
                     if constexpr (VLAW) {
-                        const Real* th = &wp(NC, i, f - 2);
-                        muf = visc_mu(a.vl, ifc(th[0], th[PX], th[2 * PX], th[3 * PX]));
+                        const Real* th = &wq(i, f - 2);
+                        muf = visc_mu(a.vl, ifc(th[0], th[QX], th[2 * QX], th[3 * QX]));
                         kf = muf * a.vl.kfac;
                     }
-                    viscous_flux_lds<Real, 1>(&wp(V, i, f - 2), &wp(NC, i, f - 2), PX, PLANE, DT + r0, DZY + r0,
+                    viscous_flux_lds<Real, 1>(&wp(V, i, f - 2), &wq(i, f - 2), PX, QX, PLANE, DT + r0, DZY + r0,
                                               DT + TL::RY + r0, DZY + TL::RY + r0, BX, muf, kf, a.inv24dy, Fd);
                     F[V] -= Fd[0];
                     F[V + 1] -= Fd[1];
@@ -1030,7 +1068,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     F[P] -= Fd[3];
                 }
 #pragma unroll
-                for (int m = 0; m < NC; m++) GL[m * TL::NFY + t] = F[m];
+                for (int m = 0; m < NC; m++) GL[m * FSZ + t] = F[m];
                 if constexpr (MODEL == DIM) UHB[t] = uh;
             }
             if (prio_tail) __builtin_amdgcn_s_setprio(0);
@@ -1040,7 +1078,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 const int fl = ty * BX + tx;
 #pragma unroll
                 for (int m = 0; m < NC; m++) {
-                    const Real d = (GL[m * TL::NFY + fl + BX] - GL[m * TL::NFY + fl]) * idy;
+                    const Real d = (GL[m * FSZ + fl + BX] - GL[m * FSZ + fl]) * idy;
                     if constexpr (ACC_LDS) slot[m * NCELL] -= d;
                     else accC[m] -= d;
                 }
