@@ -3,18 +3,16 @@
 // of the TVD-RK3 step at a fixed time step (Sec. 3.4), the reverse sweep that
 // the paper obtains by automatic differentiation (Sec. 6).
 //
-// One thread per face: it rebuilds the face's six-cell stencil (boundary
-// conditions by index mapping, as the stage kernel reads them), the two WENO
-// face states and the HLLC flux, then pulls the face cotangent
-//   Fbar_f = (Rbar_f - Rbar_{f-1}) / h        (R_i = -(F_{i+1/2} - F_{i-1/2}) / h)
-// back through HLLC, WENO5-Z and the U -> W map (reverse sweeps written out
-// below), and adds the six cells' cotangents to Ubar with atomic adds.
+// The face cotangents Fbar_f = (Rbar_f - Rbar_{f-1}) / h (R_i = -(F_{i+1/2} - F_{i-1/2}) / h)
+// are pulled back through HLLC, WENO5-Z and the U -> W map (reverse sweeps written out
+// below) along each direction by workgroups that own pieces of lines (rhs_adjoint_all).
 // Non-differentiable points take the conventions of the adjoint's reference:
 // |x|' = sgn(x) with sgn(0) = 0; min / max at a tie split the cotangent evenly; the
 // upwind switch of the HLLC flux (the sign of s*) is piecewise constant; the
 // hardware-estimate helpers rcp, rsqrt and sqrt_fast are differentiated exactly
-// (d(1/x) = -dx/x^2, ...), not through their refinement steps.  The order of the atomic additions is not fixed, so
-// the result is reproducible to round-off, not bitwise.
+// (d(1/x) = -dx/x^2, ...), not through their refinement steps.  The three directions'
+// shares meet in atomic additions whose order is not fixed, so the result is
+// reproducible to round-off, not bitwise.
 #include <hip/hip_runtime.h>
 
 #include "fv_kernels.h"
@@ -23,50 +21,55 @@ namespace fv {
 
 namespace {
 
-constexpr int ADJ_THREADS = 128;
-
-// Reverse sweep of weno5z_one: adds vb * d v / d(a, b, c, d, e) to g[0..4].
-// The forward steps are those of weno5z_one (fv_physics.h): smoothness
-// indicators, the WENO-Z factors g_k = 1 + tau/(beta_k + eps), weights scaled
-// by 10 (1, 6, 3) g_k, candidate values scaled by 6, v = N / D.
-__device__ __forceinline__ void weno5z_one_vjp(double a, double b, double c, double d, double e, double eps,
-                                               double vb, double* g)
+// Reverse sweep of weno5z_pair (fv_physics.h): adds vbm dvm/dv + vbp dvp/dv to g[0..4], the
+// cotangents of v = a, b, c, d, e.  The forward steps are those of weno5z_pair with the
+// weights written as G_k = 1 + tau / e_k.
+__device__ __forceinline__ void weno5z_pair_vjp(double a, double b, double c, double d, double e, double eps,
+                                                double vbm, double vbp, double* g)
 {
-    const double k13 = 13.0 / 12.0, q = 0.25;
-    const double t0 = a - 2.0 * b + c, s0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, s1 = b - d;
-    const double t2 = c - 2.0 * d + e, s2 = 3.0 * c - 4.0 * d + e;
-    const double b0 = k13 * t0 * t0 + q * s0 * s0;
-    const double b1 = k13 * t1 * t1 + q * s1 * s1;
-    const double b2 = k13 * t2 * t2 + q * s2 * s2;
-    const double diff = b0 - b2;
-    const double tau = ::fabs(diff);
-    const double r0 = rcp(b0 + eps), r1 = rcp(b1 + eps), r2 = rcp(b2 + eps);
-    const double al0 = 1.0 + tau * r0, al1 = 6.0 * (1.0 + tau * r1), al2 = 3.0 * (1.0 + tau * r2);
-    const double p0 = 2.0 * a - 7.0 * b + 11.0 * c;
-    const double p1 = -b + 5.0 * c + 2.0 * d;
-    const double p2 = 2.0 * c + 5.0 * d - e;
-    const double iD = rcp(6.0 * (al0 + al1 + al2));
-    const double v = (al0 * p0 + al1 * p1 + al2 * p2) * iD;
-    // reverse
-    const double Nb = vb * iD;
-    const double Db6 = -6.0 * vb * v * iD;  // 6 * dL/dD
-    const double ab0 = Nb * p0 + Db6, ab1 = Nb * p1 + Db6, ab2 = Nb * p2 + Db6;
-    const double pb0 = Nb * al0, pb1 = Nb * al1, pb2 = Nb * al2;
-    const double gb0 = ab0, gb1 = 6.0 * ab1, gb2 = 3.0 * ab2;  // dL/d(1 + tau r_k)
-    const double taub = gb0 * r0 + gb1 * r1 + gb2 * r2;
-    const double sg = diff > 0.0 ? 1.0 : (diff < 0.0 ? -1.0 : 0.0);
-    const double bb0 = -gb0 * tau * r0 * r0 + sg * taub;
-    const double bb1 = -gb1 * tau * r1 * r1;
-    const double bb2 = -gb2 * tau * r2 * r2 - sg * taub;
-    const double tb0 = 2.0 * k13 * t0 * bb0, sb0 = 2.0 * q * s0 * bb0;
-    const double tb1 = 2.0 * k13 * t1 * bb1, sb1 = 2.0 * q * s1 * bb1;
-    const double tb2 = 2.0 * k13 * t2 * bb2, sb2 = 2.0 * q * s2 * bb2;
-    g[0] += 2.0 * pb0 + tb0 + sb0;
-    g[1] += -7.0 * pb0 - pb1 - 2.0 * tb0 - 4.0 * sb0 + tb1 + sb1;
-    g[2] += 11.0 * pb0 + 5.0 * pb1 + 2.0 * pb2 + tb0 + 3.0 * sb0 - 2.0 * tb1 + tb2 + 3.0 * sb2;
-    g[3] += 2.0 * pb1 + 5.0 * pb2 + tb1 - sb1 - 2.0 * tb2 - 4.0 * sb2;
-    g[4] += -pb2 + tb2 + sb2;
+    const double k13 = 13.0 / 12.0;
+    const double d1 = b - a, d2 = c - b, d3 = d - c, d4 = e - d;
+    const double t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
+    const double h0 = fma(0.5, t0, d2), h2 = fma(-0.5, t2, d3), x = d2 + d3;
+    const double e0 = fma(h0, h0, weno5z_curvature(t0, eps)), e1 = fma(0.25 * x, x, weno5z_curvature(t1, eps));
+    const double e2 = fma(h2, h2, weno5z_curvature(t2, eps));
+    const double diff = e0 - e2, tau = ::fabs(diff);
+    const double p01 = e0 * e1, R = rcp(p01 * e2), t = e2 * R;
+    const double r0 = e1 * t, r1 = e0 * t, r2 = p01 * R;
+    const double G0 = fma(tau, r0, 1.0), G1 = fma(tau, r1, 1.0), G2 = fma(tau, r2, 1.0);
+    // + face: v_i + N / D with candidates q0, q1, q2; - face: the mirror image (u0, u1, u2)
+    const double third = 1.0 / 3.0;
+    const double q0 = fma(2.5, d2, -d1), q1 = fma(2.0, d3, d2), q2 = fma(-0.5, d4, 2.0 * d3);
+    const double u0 = fma(-2.5, d3, d4), u1 = -fma(2.0, d2, d3), u2 = fma(0.5, d1, -2.0 * d2);
+    const double im = rcp(fma(3.0, G2, fma(6.0, G1, G0))), ip = rcp(fma(3.0, G0, fma(6.0, G1, G2)));
+    const double nm = vbm * im, np = vbp * ip;  // cotangents of the numerators
+    const double dm = -nm * im * fma(third * G0, q0, fma(G1, q1, G2 * q2));  // and of the denominators
+    const double dp = -np * ip * fma(third * G2, u0, fma(G1, u1, G0 * u2));
+    const double b0 = fma(third * nm, q0, dm) + fma(np, u2, 3.0 * dp);
+    const double b1 = fma(nm, q1, 6.0 * dm) + fma(np, u1, 6.0 * dp);
+    const double b2 = fma(nm, q2, 3.0 * dm) + fma(third * np, u0, dp);
+    const double qb0 = third * nm * G0, qb1 = nm * G1, qb2 = nm * G2;
+    const double ub0 = third * np * G2, ub1 = np * G1, ub2 = np * G0;
+    double db1 = fma(0.5, ub2, -qb0), db4 = fma(-0.5, qb2, ub0);
+    double db2 = fma(2.5, qb0, qb1) - 2.0 * (ub1 + ub2);
+    double db3 = 2.0 * (qb1 + qb2) - fma(2.5, ub0, ub1);
+    // G_k = 1 + tau / e_k, tau = |e0 - e2|
+    const double taub = fma(b0, r0, fma(b1, r1, b2 * r2));
+    const double sg = diff > 0.0 ? taub : (diff < 0.0 ? -taub : 0.0);
+    const double eb0 = fma(-b0 * tau * r0, r0, sg), eb1 = -b1 * tau * r1 * r1, eb2 = fma(-b2 * tau * r2, r2, -sg);
+    // e_k = 13/12 t_k^2 + (its first-difference term)^2 + eps
+    const double hb0 = 2.0 * h0 * eb0, hb2 = 2.0 * h2 * eb2, xb = 0.5 * x * eb1;
+    const double tb0 = fma(2.0 * k13 * t0, eb0, 0.5 * hb0), tb1 = 2.0 * k13 * t1 * eb1;
+    const double tb2 = fma(2.0 * k13 * t2, eb2, -0.5 * hb2);
+    db1 -= tb0;
+    db2 += hb0 + xb + tb0 - tb1;
+    db3 += hb2 + xb + tb1 - tb2;
+    db4 += tb2;
+    g[0] -= db1;
+    g[1] += db1 - db2;
+    g[2] += db2 - db3 + (vbm + vbp);
+    g[3] += db3 - db4;
+    g[4] += db4;
 }
 
 // Reverse sweep of the single-phase U -> W map: Ub = (dW/dU)^T Wb.
@@ -182,25 +185,28 @@ __device__ __forceinline__ void hllc_vjp(const Material<double>& mat, const doub
     const double rd = rcp(mL - mR);
     const double sstar = num * rd;
     const double sminus = ::fmin(0.0, sL), splus = ::fmax(0.0, sR);
-    // star-side fluxes
-    double sLb = 0.0, sRb = 0.0, smb = 0.0, spb = 0.0, sstarb = 0.0;
-    if (sstar == 0.0) {
-        double gh[NC];
+    // star-side flux of the upwind side, chosen by operand selection as in the forward; both
+    // sides with half the cotangent where s* = 0
+    const bool left = !(sstar < 0.0), both = sstar == 0.0;
+    double ws[NC], gs[NC], wsb[NC];
 #pragma unroll
-        for (int m = 0; m < NC; m++) gh[m] = 0.5 * g[m];
-        double kb, wb, sb;
-        hllc_side_vjp<DIR>(mat, wl, sL, sminus, sstar, gh, wlb, kb, wb, sb);
-        sLb += kb;
-        smb += wb;
+    for (int m = 0; m < NC; m++) {
+        ws[m] = left ? wl[m] : wr[m];
+        gs[m] = both ? 0.5 * g[m] : g[m];
+        wsb[m] = 0.0;
+    }
+    double sKb, swb, sstarb;
+    hllc_side_vjp<DIR>(mat, ws, left ? sL : sR, left ? sminus : splus, sstar, gs, wsb, sKb, swb, sstarb);
+    double sLb = left ? sKb : 0.0, sRb = left ? 0.0 : sKb, smb = left ? swb : 0.0, spb = left ? 0.0 : swb;
+#pragma unroll
+    for (int m = 0; m < NC; m++) {
+        wlb[m] += left ? wsb[m] : 0.0;
+        wrb[m] += left ? 0.0 : wsb[m];
+    }
+    if (both) {
+        double sb;
+        hllc_side_vjp<DIR>(mat, wr, sR, splus, sstar, gs, wrb, sRb, spb, sb);
         sstarb += sb;
-        hllc_side_vjp<DIR>(mat, wr, sR, splus, sstar, gh, wrb, kb, wb, sb);
-        sRb += kb;
-        spb += wb;
-        sstarb += sb;
-    } else if (!(sstar < 0.0)) {
-        hllc_side_vjp<DIR>(mat, wl, sL, sminus, sstar, g, wlb, sLb, smb, sstarb);
-    } else {
-        hllc_side_vjp<DIR>(mat, wr, sR, splus, sstar, g, wrb, sRb, spb, sstarb);
     }
     // s^- = min(0, sL), s^+ = max(0, sR)
     sLb += smb * (sL < 0.0 ? 1.0 : (sL == 0.0 ? 0.5 : 0.0));
@@ -261,140 +267,302 @@ __device__ __forceinline__ void hllc_vjp(const Material<double>& mat, const doub
     wrb[P] += pRb;
 }
 
+// ---- the right-hand side's adjoint.  A workgroup owns LN lines along one direction and,
+// of each, the cells [i0, i1); thread (line, slot) holds the line position p = i0 - 3 + slot
+// (a position may lie outside the domain: it is mapped by the boundary conditions) and
+// works in turn on
+//   cell p   conversion to primitive variables (staged in LDS, two more positions on
+//            either side) and both WENO5-Z values of the cell;
+//   face p   (between p - 1 and p) the reverse sweep of HLLC with the face's cotangent,
+//            in place of the two face states;
+//   cell p   the reverse sweep of its reconstruction: cotangents of positions p-2 .. p+2,
+//            collected across the threads through LDS;
+//   cell p   the cotangents of halo positions added to the cells they mirror, the reverse
+//            sweep of U -> W, and the sum into Ubar.
+// A periodic line that fits a workgroup closes on itself (positions 0 .. n-1, no halo).
+// What bounds it: the latency of that chain (~1700 vector instructions) at three waves per
+// SIMD.  A thread per face, which rebuilt ten cell reconstructions and added 30 values with
+// atomics at one wave per SIMD, took 214 us per right-hand side at 64^3; this takes 69
+// (24^3: 12).  Measured for the 5-step gradient at 64^3 / 24^3: 256 threads at three
+// waves per SIMD 2.29 / 1.44 ms, at four (spills) 2.54 / 1.47, 512 threads at four 2.45 /
+// 1.51, 128 threads at three 2.75 / 1.47.  One launch for the three directions, meeting in
+// five atomic additions per cell and direction, against three launches that add without
+// atomics: 2.45 against 2.62 ms, at 24^3 1.51 against 1.98, at 128^3 equal within 1 %.
+constexpr int ADJ_NT = 256;    // threads of a workgroup
+constexpr int ADJ_CELLS = 64;  // longest piece of a line in one workgroup
+
+// pieces of a line: all of it when periodic and short, else equal pieces of at most
+// ADJ_CELLS cells (of 32 or more when there are several, so that a boundary's three halo
+// positions and their mirror images lie in one piece); slots = positions per line
+struct AdjointSplit {
+    int pieces, slots, lines;  // per line; per piece; lines of a workgroup
+    bool closed;               // the line closes on itself
+};
+
+__host__ __device__ inline AdjointSplit adjoint_split(int n, bool periodic)
+{
+    AdjointSplit s;
+    s.closed = periodic && n <= ADJ_CELLS + 7;
+    s.pieces = s.closed ? 1 : (n + ADJ_CELLS - 1) / ADJ_CELLS;
+    s.slots = s.closed ? n : (n + s.pieces - 1) / s.pieces + 7;
+    s.lines = ADJ_NT / s.slots;
+    return s;
+}
+
+struct AdjointLds {
+    // primitive states of the slots and, in pieces of a line, of two more positions on
+    // either side (4 lines <= ADJ_NT / 2 entries: a piece has at least 8 slots)
+    double W[5][ADJ_NT + ADJ_NT / 2];
+    // face states, then their cotangents, then the exchanged cotangents of neighbouring cells
+    double X[10][ADJ_NT];
+};
+
 template <int DIR>
-__device__ __forceinline__ void face_adjoint_body(const AdjointArgs& a, const double ih, const long long t,
-                                                  const double* __restrict__ U, const double* __restrict__ Rbar,
-                                                  double* __restrict__ Ubar)
+__device__ __forceinline__ void rhs_adjoint_body(AdjointLds& lds, const AdjointArgs& a, const AdjointSplit& sp,
+                                                 unsigned block,
+                                                 const double* __restrict__ U, const double* __restrict__ Rbar,
+                                                 double* __restrict__ Ubar, const double scale)
 {
     constexpr int NC = 5, V = 1;
+    const double ih = (DIR == 0 ? a.idx : (DIR == 1 ? a.idy : a.idz)) * scale;
+    auto& W = lds.W;
+    auto& X = lds.X;
     const int n = DIR == 0 ? a.nx : (DIR == 1 ? a.ny : a.nz);
-    const long long lines = a.ncell / n;
-    if (t >= lines * (n + 1)) return;
-    // consecutive threads take consecutive x: along the line for x faces, across the
-    // lines for y and z faces (coalesced loads and accumulations)
-    int f;           // face f lies between cells f-1 and f of the line
-    int ci, cj, ck;  // coordinates of the line's cells; the DIR one is set per cell below
+    const int SL = sp.slots, LN = sp.lines;
+    const bool periodic = a.bc[2 * DIR] == PERIODIC;
+    const int tid = threadIdx.x;
+    // (slot, line): along x the slots are consecutive in memory, else the lines are
+    const int slot = DIR == 0 ? tid % SL : tid / LN, ln = DIR == 0 ? tid / SL : tid % LN;
+    const bool active = DIR == 0 ? ln < LN : slot < SL;
+    // lines < 2^32: a state of that many cells would not fit the memory
+    const unsigned nx = (unsigned)a.nx;
+    const unsigned nlines = DIR == 0 ? (unsigned)a.ny * (unsigned)a.nz : nx * (unsigned)(DIR == 1 ? a.nz : a.ny);
+    unsigned piece = 0;
+    if (sp.pieces > 1) {
+        piece = block % (unsigned)sp.pieces;
+        block /= (unsigned)sp.pieces;
+    }
+    const unsigned line = block * (unsigned)LN + (unsigned)ln;
+    const bool on = active && line < nlines;
+    // equal pieces: the first `longer` ones have a cell more
+    const int len = n / sp.pieces, longer = n - len * sp.pieces;
+    const int i0 = len * (int)piece + min((int)piece, longer), i1 = i0 + len + ((int)piece < longer ? 1 : 0);
+    const int p0 = sp.closed ? 0 : i0 - 3;
+    const int p = p0 + slot;
+    // cell 0 of the line and the stride along it
+    long long base, stride;
     if (DIR == 0) {
-        f = (int)(t % (n + 1));
-        const long long line = t / (n + 1);
-        ci = 0;
-        cj = (int)(line % a.ny);
-        ck = (int)(line / a.ny);
+        base = (long long)line * n;
+        stride = 1;
+    } else if (DIR == 1) {
+        const unsigned k = line / nx;
+        base = (long long)k * a.ny * a.nx + (line - k * nx);
+        stride = a.nx;
     } else {
-        ci = (int)(t % a.nx);
-        const long long r = t / a.nx;
-        f = (int)(r % (n + 1));
-        const int o = (int)(r / (n + 1));
-        cj = DIR == 1 ? 0 : o;
-        ck = DIR == 1 ? o : 0;
+        base = line;
+        stride = (long long)a.nx * a.ny;
     }
-    const long long stride = DIR == 0 ? 1 : (DIR == 1 ? (long long)a.nx : (long long)a.nx * a.ny);
-    const long long base = ((long long)ck * a.ny + cj) * a.nx + ci;  // cell 0 of the line
-    const int blo = a.bc[2 * DIR], bhi = a.bc[2 * DIR + 1];
     const Material<double> mat = a.mat;
+    auto at = [&](int s) { return DIR == 0 ? ln * SL + s : s * LN + ln; };          // X entry of a slot
+    const int SR = sp.closed ? SL : SL + 4;                                         // staged positions
+    auto row = [&](int r) { return DIR == 0 ? ln * SR + r : r * LN + ln; };         // W entry of a staged position
+    auto wrap = [&](int s) {  // slots -2 .. SL + 1 of a closed line (of one cell or more)
+        s += s < 0 ? SL : 0;
+        s += s < 0 ? SL : 0;
+        s -= s >= SL ? SL : 0;
+        return s >= SL ? s - SL : s;
+    };
 
-    // stencil cells f-3 .. f+2: mapped index, mirror flag and primitive state
-    long long q[6];
-    bool flip[6];
-    double w[6][NC];
+    // ---- loads, all issued before the first is used: the state at the position and, for the
+    // first four slots of a piece, at one of the four positions beyond its slots; Rbar of the
+    // two cells of the face below p (in bounds for every thread, set to zero where the face
+    // or the cell does not exist)
+    double u[NC], uh[NC], rl[NC], rr[NC], g[NC];
+    bool fl = false, flh = false;
+    const bool second = SL + slot < SR;
+    if (on) {
+        const long long q = base + map_index(sp.closed ? slot : i0 - 5 + slot, n, a.bc[2 * DIR], a.bc[2 * DIR + 1], fl) * stride;
+        const long long qh =
+            second ? base + map_index(i0 - 5 + SL + slot, n, a.bc[2 * DIR], a.bc[2 * DIR + 1], flh) * stride : q;
+        int lo = p - 1, hi = p;
+        if (periodic) {
+            lo += lo < 0 ? n : 0;  // p - 1 >= -1, or n > ADJ_CELLS + 7
+            hi += hi < 0 ? n : 0;
+            lo -= lo >= n ? n : 0;
+            hi -= hi >= n ? n : 0;
+        }
+        const long long ql = base + min(max(lo, 0), n - 1) * stride, qr = base + min(max(hi, 0), n - 1) * stride;
 #pragma unroll
-    for (int s = 0; s < 6; s++) {
-        bool fl = false;
-        const int g = map_index(f - 3 + s, n, blo, bhi, fl);
-        q[s] = base + g * stride;
-        flip[s] = fl;
-        double u[NC];
+        for (int m = 0; m < NC; m++) u[m] = U[m * a.ncell + q];
+        if (second)
 #pragma unroll
-        for (int m = 0; m < NC; m++) u[m] = U[m * a.ncell + q[s]];
-        if (fl) u[V + DIR] = -u[V + DIR];
-        cons_to_prim<double, EULER>(mat, u, w[s]);
-    }
-    // cotangent of the face flux
-    double g[NC];
+            for (int m = 0; m < NC; m++) uh[m] = U[m * a.ncell + qh];
 #pragma unroll
-    for (int m = 0; m < NC; m++) {
-        double v = 0.0;
-        if (f < n) v += Rbar[m * a.ncell + base + f * stride];
-        if (f >= 1) v -= Rbar[m * a.ncell + base + (f - 1) * stride];
-        g[m] = v * ih;
-    }
-    // face states: left = v^- of cell f-1 (stencil slots 0..4), right = v^+ of cell f (slots
-    // 1..5, the mirrored stencil); the same values as the stage kernel's pair reconstruction
-    double wl[NC], wr[NC];
-#pragma unroll
-    for (int m = 0; m < NC; m++) {
-        double vm, vp, x0, x1;
-        weno5z_pair(w[0][m], w[1][m], w[2][m], w[3][m], w[4][m], a.weps, vm, x0);
-        weno5z_pair(w[1][m], w[2][m], w[3][m], w[4][m], w[5][m], a.weps, x1, vp);
-        wl[m] = vm;
-        wr[m] = vp;
-    }
-    // HLLC: cotangents of the two face states
-    double wlb[NC], wrb[NC];
-#pragma unroll
-    for (int m = 0; m < NC; m++) {
-        wlb[m] = 0.0;
-        wrb[m] = 0.0;
-    }
-    hllc_vjp<DIR>(mat, wl, wr, g, wlb, wrb);
-    // WENO5-Z: cotangents of the stencil's primitive states (reverse sweeps)
-    double wb[6][NC];
-#pragma unroll
-    for (int s = 0; s < 6; s++)
-#pragma unroll
-        for (int m = 0; m < NC; m++) wb[s][m] = 0.0;
-#pragma unroll
-    for (int m = 0; m < NC; m++) {
-        double gl[5] = {0, 0, 0, 0, 0}, gr[5] = {0, 0, 0, 0, 0};
-        weno5z_one_vjp(w[0][m], w[1][m], w[2][m], w[3][m], w[4][m], a.weps, wlb[m], gl);
-        weno5z_one_vjp(w[5][m], w[4][m], w[3][m], w[2][m], w[1][m], a.weps, wrb[m], gr);
-#pragma unroll
-        for (int k = 0; k < 5; k++) {
-            wb[k][m] += gl[k];
-            wb[5 - k][m] += gr[k];
+        for (int m = 0; m < NC; m++) {
+            rl[m] = Rbar[m * a.ncell + ql];
+            rr[m] = Rbar[m * a.ncell + qr];
         }
     }
-    // U -> W, then the boundary mapping
+    __builtin_amdgcn_sched_barrier(0);
+    // faces -1 and below, n + 1 and above of a line with boundaries have no cotangent
+    const bool face = on && (sp.closed || slot > 0) && (periodic || (p >= 0 && p <= n));
+    auto stage = [&](int r, double* v, bool flip) {
+        if (flip) v[V + DIR] = -v[V + DIR];
+        double w[NC];
+        cons_to_prim<double, EULER>(mat, v, w);
 #pragma unroll
-    for (int s = 0; s < 6; s++) {
-        double ub[NC];
-        cons_to_prim_vjp(mat, w[s], wb[s], ub);
-        if (flip[s]) ub[V + DIR] = -ub[V + DIR];
+        for (int m = 0; m < NC; m++) W[m][row(r)] = w[m];
+    };
+    if (on) {
+        stage(slot, u, fl);
+        if (second) stage(SL + slot, uh, flh);
 #pragma unroll
-        for (int m = 0; m < NC; m++) atomicAdd(&Ubar[m * a.ncell + q[s]], ub[m]);
+        for (int m = 0; m < NC; m++) {
+            const double v = (periodic || p < n ? rr[m] : 0.0) - (periodic || p >= 1 ? rl[m] : 0.0);
+            g[m] = v * ih;
+        }
+    }
+    __syncthreads();
+    // the five staged positions around the thread's
+    int r5[5];
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        r5[k] = row(sp.closed ? wrap(slot + k - 2) : slot + k);
+    }
+    // ---- both reconstructed values of the cell: X[m] the one at its + face, X[5 + m] at its - face
+    if (on) {
+#pragma unroll
+        for (int m = 0; m < NC; m++) {
+            double vm, vp;
+            weno5z_pair(W[m][r5[0]], W[m][r5[1]], W[m][r5[2]], W[m][r5[3]], W[m][r5[4]], a.weps, vm, vp);
+            X[m][at(slot)] = vm;
+            X[NC + m][at(slot)] = vp;
+        }
+    }
+    __syncthreads();
+    // ---- the face's states replaced by their cotangents (each is read by this thread only)
+    if (on && (sp.closed || slot > 0)) {
+        const int el = at(sp.closed ? wrap(slot - 1) : slot - 1), er = at(slot);
+        double wlb[NC], wrb[NC];
+#pragma unroll
+        for (int m = 0; m < NC; m++) wlb[m] = wrb[m] = 0.0;
+        if (face) {
+            double wl[NC], wr[NC];
+#pragma unroll
+            for (int m = 0; m < NC; m++) {
+                wl[m] = X[m][el];
+                wr[m] = X[NC + m][er];
+            }
+            hllc_vjp<DIR>(mat, wl, wr, g, wlb, wrb);
+        }
+#pragma unroll
+        for (int m = 0; m < NC; m++) {
+            X[m][el] = wlb[m];
+            X[NC + m][er] = wrb[m];
+        }
+    }
+    __syncthreads();
+    // ---- reverse sweep of the cell's reconstruction, and the cotangent of the position
+    const bool cell = on && (sp.closed || (slot > 0 && slot < SL - 1));
+    double cm[NC], cp[NC], wb[NC];
+#pragma unroll
+    for (int m = 0; m < NC; m++) {
+        cm[m] = cell ? X[m][at(slot)] : 0.0;
+        cp[m] = cell ? X[NC + m][at(slot)] : 0.0;
+        wb[m] = 0.0;
+    }
+    // the exchange needs four of the ten arrays per component: two components at a time
+    // (the position's own share stays in a register)
+    constexpr int K4[4] = {0, 1, 3, 4};
+    auto nb = [&](int k) {  // entry of the cell whose k-th cotangent belongs to this position
+        const int s = sp.closed ? wrap(slot + 2 - k) : slot + 2 - k;
+        return s >= 0 && s < SL ? at(s) : -1;
+    };
+#pragma unroll
+    for (int m0 = 0; m0 < NC; m0 += 2) {
+        __syncthreads();  // the arrays' last readers are done
+#pragma unroll
+        for (int m = m0; m < m0 + 2 && m < NC; m++) {
+            double gs[5] = {0, 0, 0, 0, 0};
+            if (cell)
+                weno5z_pair_vjp(W[m][r5[0]], W[m][r5[1]], W[m][r5[2]], W[m][r5[3]], W[m][r5[4]], a.weps, cm[m], cp[m], gs);
+            wb[m] = gs[2];
+            if (on)
+#pragma unroll
+                for (int k = 0; k < 4; k++) X[4 * (m - m0) + k][at(slot)] = gs[K4[k]];
+        }
+        __syncthreads();
+        if (on)
+#pragma unroll
+            for (int m = m0; m < m0 + 2 && m < NC; m++)
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const int e = nb(K4[k]);
+                    if (e >= 0) wb[m] += X[4 * (m - m0) + k][e];
+                }
+    }
+    // ---- halo positions of a boundary (not periodic): added to the cell they mirror
+    if (!periodic && (i0 == 0 || i1 == n)) {  // uniform
+        __syncthreads();
+        if (on)
+#pragma unroll
+            for (int m = 0; m < NC; m++) X[m][at(slot)] = wb[m];
+        __syncthreads();
+        if (on && p >= i0 && p < i1) {
+#pragma unroll
+            for (int side = 0; side < 2; side++) {
+                if (side == 0 ? i0 != 0 : i1 != n) continue;
+                for (int h = 0; h < 3; h++) {
+                    const int q = side == 0 ? -1 - h : n + h;
+                    bool fl = false;
+                    if (map_index(q, n, a.bc[2 * DIR], a.bc[2 * DIR + 1], fl) != p) continue;
+#pragma unroll
+                    for (int m = 0; m < NC; m++) {
+                        const double v = X[m][at(q - p0)];
+                        wb[m] += fl && m == V + DIR ? -v : v;
+                    }
+                }
+            }
+        }
+    }
+    // ---- U -> W, summed over the directions
+    if (on && p >= i0 && p < i1) {
+        double w[NC], ub[NC];
+        const int rc = r5[2];
+#pragma unroll
+        for (int m = 0; m < NC; m++) w[m] = W[m][rc];
+        cons_to_prim_vjp(mat, w, wb, ub);
+        const long long q = base + p * stride;
+#pragma unroll
+        for (int m = 0; m < NC; m++) {
+            atomicAdd(&Ubar[m * a.ncell + q], ub[m]);
+        }
     }
 }
 
-// The three directions in one launch: blocks [0, b1) take the x faces, [b1, b2) the y
-// faces, the rest the z faces.  At one wave per SIMD a 64^3 direction alone fills about
-// four rounds of workgroups and a nearly empty fifth; one launch for all three leaves a
-// single partial round (RHS adjoint at 64^3 0.257 -> 0.222 ms).
-__global__ void __launch_bounds__(ADJ_THREADS) face_adjoint_all(const AdjointArgs a, const unsigned b1, const unsigned b2,
-                                                                const double* __restrict__ U,
-                                                                const double* __restrict__ Rbar,
-                                                                double* __restrict__ Ubar)
+// the three directions in one launch: blocks [0, b1) take x, [b1, b2) y, the rest z
+__global__ void __launch_bounds__(ADJ_NT, 3) rhs_adjoint_all(const AdjointArgs a, const AdjointSplit sx,
+                                                            const AdjointSplit sy, const AdjointSplit sz,
+                                                            const unsigned b1, const unsigned b2,
+                                                            const double* __restrict__ U,
+                                                            const double* __restrict__ Rbar,
+                                                            double* __restrict__ Ubar, const double scale)
 {
+    __shared__ AdjointLds lds;
     const unsigned b = blockIdx.x;
-    if (b < b1) face_adjoint_body<0>(a, a.idx, (long long)b * ADJ_THREADS + threadIdx.x, U, Rbar, Ubar);
-    else if (b < b2) face_adjoint_body<1>(a, a.idy, (long long)(b - b1) * ADJ_THREADS + threadIdx.x, U, Rbar, Ubar);
-    else face_adjoint_body<2>(a, a.idz, (long long)(b - b2) * ADJ_THREADS + threadIdx.x, U, Rbar, Ubar);
+    if (b < b1) rhs_adjoint_body<0>(lds, a, sx, b, U, Rbar, Ubar, scale);
+    else if (b < b2) rhs_adjoint_body<1>(lds, a, sy, b - b1, U, Rbar, Ubar, scale);
+    else rhs_adjoint_body<2>(lds, a, sz, b - b2, U, Rbar, Ubar, scale);
 }
 
-__global__ void fill_zero_kernel(double* __restrict__ p, long long n)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-        p[i] = 0.0;
-}
-
-// out = c0 x0 + c1 x1 + c2 x2 + c3 x3 (null x terms are skipped); out may alias an input
+// out = c0 x0 + c1 x1 + c2 x2 (null terms are skipped); out may alias an input
 __global__ void lincomb_kernel(double* out, long long n, double c0, const double* x0, double c1, const double* x1,
-                               double c2, const double* x2, double c3, const double* x3)
+                               double c2, const double* x2)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        double v = c0 * x0[i];
+        double v = x0 ? c0 * x0[i] : 0.0;
         if (x1) v += c1 * x1[i];
         if (x2) v += c2 * x2[i];
-        if (x3) v += c3 * x3[i];
         out[i] = v;
     }
 }
@@ -407,26 +575,26 @@ int grid_for(long long n, int threads)
 
 }  // namespace
 
-hipError_t launch_rhs_adjoint(const AdjointArgs& a, const double* U, const double* Rbar, double* Ubar, hipStream_t st)
+hipError_t launch_rhs_adjoint(const AdjointArgs& a, const double* U, const double* Rbar, double* Ubar, double scale,
+                              hipStream_t st)
 {
-    const long long total = a.ncell * 5;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, Ubar, total);
-    unsigned blocks[3];
+    const int n3[3] = {a.nx, a.ny, a.nz};
+    AdjointSplit sp[3];
+    unsigned blocks[3], total = 0;
     for (int d = 0; d < 3; d++) {
-        const int n = d == 0 ? a.nx : (d == 1 ? a.ny : a.nz);
-        const long long faces = a.ncell / n * (n + 1);
-        blocks[d] = (unsigned)((faces + ADJ_THREADS - 1) / ADJ_THREADS);
+        sp[d] = adjoint_split(n3[d], a.bc[2 * d] == PERIODIC);
+        blocks[d] = (unsigned)((a.ncell / n3[d] + sp[d].lines - 1) / sp[d].lines * sp[d].pieces);
+        total += blocks[d];
     }
-    hipLaunchKernelGGL(face_adjoint_all, dim3(blocks[0] + blocks[1] + blocks[2]), dim3(ADJ_THREADS), 0, st, a, blocks[0],
-                       blocks[0] + blocks[1], U, Rbar, Ubar);
+    hipLaunchKernelGGL(rhs_adjoint_all, dim3(total), dim3(ADJ_NT), 0, st, a, sp[0], sp[1], sp[2], blocks[0],
+                       blocks[0] + blocks[1], U, Rbar, Ubar, scale);
     return hipGetLastError();
 }
 
 hipError_t launch_lincomb(double* out, long long n, double c0, const double* x0, double c1, const double* x1, double c2,
-                          const double* x2, double c3, const double* x3, hipStream_t st)
+                          const double* x2, hipStream_t st)
 {
-    hipLaunchKernelGGL(lincomb_kernel, dim3(grid_for(n, 256)), dim3(256), 0, st, out, n, c0, x0, c1, x1, c2, x2, c3,
-                       x3);
+    hipLaunchKernelGGL(lincomb_kernel, dim3(grid_for(n, 256)), dim3(256), 0, st, out, n, c0, x0, c1, x1, c2, x2);
     return hipGetLastError();
 }
 

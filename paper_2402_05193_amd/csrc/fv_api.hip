@@ -718,8 +718,12 @@ int rhs_adjoint(const fv_config* cfg, const void* U, const void* Rbar, void* Uba
     (void)ws;
     if ((r = check_ptr(U, "U")) || (r = check_ptr(Rbar, "Rbar")) || (r = check_ptr(Ubar, "Ubar"))) return r;
     if (Ubar == U || Ubar == Rbar) return fail(FV_EINVAL, "Ubar must not overlap U or Rbar");
-    hipError_t e = fv::launch_rhs_adjoint(adjoint_args(cfg), (const double*)U, (const double*)Rbar, (double*)Ubar,
-                                          (hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    // cleared by a kernel, 8 bytes a value, so that the call can be captured
+    const long long n = 5ll * cfg->nx * cfg->ny * cfg->nz;
+    hipError_t e = fv::launch_lincomb((double*)Ubar, n, 0.0, nullptr, 0.0, nullptr, 0.0, nullptr, st);
+    if (e == hipSuccess)
+        e = fv::launch_rhs_adjoint(adjoint_args(cfg), (const double*)U, (const double*)Rbar, (double*)Ubar, 1.0, st);
     if (e != hipSuccess) return hip_fail(e, "rhs_adjoint");
     return FV_OK;
 }
@@ -737,8 +741,8 @@ int adjoint_workspace_bytes(const fv_config* cfg, size_t* out)
 
 // Reverse sweep of one TVD-RK3 step from its stage states U1, U2 (Sec. 3.4):
 // U1 = Un + dt R(Un); U2 = 3/4 Un + 1/4 U1 + 1/4 dt R(U1); U3 = 1/3 Un + 2/3 U2 + 2/3 dt R(U2).
-// On entry Ubar holds the cotangent of U3, on return that of Un.  aws holds G2, G1 and T
-// at state slots 2, 3 and 4 (slots 0 and 1 are free for the caller's stage states).
+// On entry Ubar holds the cotangent of U3, on return that of Un.  aws holds G2 and G1 at
+// state slots 2 and 3 (slots 0 and 1 are free for the caller's stage states).
 static int step_adjoint_sweep(const fv_config* cfg, const void* Un, const void* U1p, const void* U2p, void* Ubar,
                               double dt, void* aws, hipStream_t st)
 {
@@ -747,16 +751,16 @@ static int step_adjoint_sweep(const fv_config* cfg, const void* Un, const void* 
     const double* U2 = (const double*)U2p;
     double* G2 = (double*)((char*)aws + 2 * sb);
     double* G1 = (double*)((char*)aws + 3 * sb);
-    double* T = (double*)((char*)aws + 4 * sb);
     double* G3 = (double*)Ubar;
     const long long n = 5ll * cfg->nx * cfg->ny * cfg->nz;
     const fv::AdjointArgs a = adjoint_args(cfg);
-    hipError_t e = fv::launch_rhs_adjoint(a, U2, G3, T, st);
-    if (e == hipSuccess) e = fv::launch_lincomb(G2, n, 2.0 / 3.0, G3, 2.0 / 3.0 * dt, T, 0, nullptr, 0, nullptr, st);
-    if (e == hipSuccess) e = fv::launch_rhs_adjoint(a, U1, G2, T, st);
-    if (e == hipSuccess) e = fv::launch_lincomb(G1, n, 0.25, G2, 0.25 * dt, T, 0, nullptr, 0, nullptr, st);
-    if (e == hipSuccess) e = fv::launch_rhs_adjoint(a, (const double*)Un, G1, T, st);
-    if (e == hipSuccess) e = fv::launch_lincomb(G3, n, 1.0 / 3.0, G3, 0.75, G2, 1.0, G1, dt, T, st);
+    // each right-hand side's share is added to the rest of its stage's cotangent
+    hipError_t e = fv::launch_lincomb(G2, n, 2.0 / 3.0, G3, 0, nullptr, 0, nullptr, st);
+    if (e == hipSuccess) e = fv::launch_rhs_adjoint(a, U2, G3, G2, 2.0 / 3.0 * dt, st);
+    if (e == hipSuccess) e = fv::launch_lincomb(G1, n, 0.25, G2, 0, nullptr, 0, nullptr, st);
+    if (e == hipSuccess) e = fv::launch_rhs_adjoint(a, U1, G2, G1, 0.25 * dt, st);
+    if (e == hipSuccess) e = fv::launch_lincomb(G3, n, 1.0 / 3.0, G3, 0.75, G2, 1.0, G1, st);
+    if (e == hipSuccess) e = fv::launch_rhs_adjoint(a, (const double*)Un, G1, G3, dt, st);
     if (e != hipSuccess) return hip_fail(e, "rk3_step_adjoint");
     return FV_OK;
 }

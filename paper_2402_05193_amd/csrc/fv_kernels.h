@@ -173,10 +173,11 @@ struct AdjointArgs {
     double weps;
     double idx, idy, idz;
 };
-// Ubar = (dR/dU)^T Rbar (overwritten), FP64
-hipError_t launch_rhs_adjoint(const AdjointArgs& a, const double* U, const double* Rbar, double* Ubar, hipStream_t st);
-// out = c0 x0 + c1 x1 + c2 x2 + c3 x3 over n values (null x1..x3 skipped; out may alias)
+// Ubar += scale (dR/dU)^T Rbar, FP64
+hipError_t launch_rhs_adjoint(const AdjointArgs& a, const double* U, const double* Rbar, double* Ubar, double scale,
+                              hipStream_t st);
+// out = c0 x0 + c1 x1 + c2 x2 over n values (null terms skipped; out may alias)
 hipError_t launch_lincomb(double* out, long long n, double c0, const double* x0, double c1, const double* x1, double c2,
-                          const double* x2, double c3, const double* x3, hipStream_t st);
+                          const double* x2, hipStream_t st);
 
 }  // namespace fv

@@ -94,6 +94,26 @@ def test_rhs_adjoint_matches_oracle_vjp(name):
     assert r <= 1e-11
 
 
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("n,bc", [(1, WL.PERIODIC), (2, WL.PERIODIC), (71, WL.PERIODIC), (72, WL.PERIODIC),
+                                  (129, WL.PERIODIC), (1, WL.ZERO_GRADIENT), (64, WL.ZERO_GRADIENT),
+                                  (65, WL.ZERO_GRADIENT), (3, WL.SYMMETRY), (65, WL.SYMMETRY), (131, WL.SYMMETRY)])
+def test_rhs_adjoint_line_pieces(n, bc, axis):
+    """Lines at the edges of the kernel's pieces: periodic ones that close on themselves
+    (up to 71 cells) or are cut, and boundaries at the ends of one or several pieces
+    (64 cells at most).  Bar: that of test_rhs_adjoint_matches_oracle_vjp."""
+    shape, bcs = [4, 4, 4], [WL.PERIODIC] * 6
+    shape[axis] = n
+    bcs[2 * axis] = bcs[2 * axis + 1] = bc
+    oc, U, cfg = setup(rough(tuple(shape), tuple(bcs), seed=n))
+    rng = np.random.default_rng(7)
+    Rbar = rng.standard_normal(U.shape)
+    ref = ET.rhs_vjp(oc, torch.from_numpy(U), torch.from_numpy(Rbar)).numpy()
+    Ubar = torch.full_like(dev(U), float("nan"))
+    S.rhs_adjoint(cfg, dev(U), dev(Rbar), Ubar)
+    assert rel(Ubar.cpu().numpy(), ref) <= 1e-11
+
+
 def test_dot_product_identity():
     oc, U, cfg = setup_named("rough_periodic")
     rng = np.random.default_rng(6)
