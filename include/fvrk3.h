@@ -176,9 +176,8 @@ int rhs_ws(const fv_config* cfg, const void* U, void* R, double dt, void* ws, vo
 
 /* Workgroups of the problem's share of a batched stage launch; a measure of how
  * much of the GPU the problem fills (each CU holds two FP64 or three FP32 stage
- * workgroups at a time).  A single-problem launch has as many, except that the
- * five-equation model may take fewer, longer z chunks alone when they still give
- * every CU its full share. */
+ * workgroups at a time).  A single-problem launch chooses its z chunks, and so its
+ * number of workgroups, by itself (results do not depend on them). */
 int stage_workgroups(const fv_config* cfg, int32_t* out);
 
 /* Bytes of the limiter decision record of rhs_flags: one byte per cell face,

@@ -39,41 +39,24 @@ size_t state_bytes(const fv_config* c)
     return es * (size_t)ncomp_of(c->model) * (size_t)c->nx * (size_t)c->ny * (size_t)c->nz;
 }
 
-// workgroups a stage launch aims at (tile columns x z chunks), FP64 and FP32 (its
-// kernels hold fewer registers, more workgroups fit a CU).  Measured at 256^3 (NS,
-// stage ms): FP64 512 / 1024 / 2048 / 4096 workgroups 2.58 / 2.54 / 2.51 / 2.53;
-// FP32 (three waves per SIMD) 3072 / 4096 / 6144 / 8192 workgroups 1.41 / 1.36 /
-// 1.36 / 1.36, the Euler and five-equation stages alike within 1 %.
+// z chunks of batched members: a launch aims at FV_TARGET_WORKGROUPS workgroups (tile
+// columns x z chunks), FP64 and FP32 (its kernels hold fewer registers, more workgroups fit
+// a CU), with chunks of at least FV_MIN_ZCHUNK planes, unless the member alone would then
+// have fewer workgroups than the GPU holds at once (2 FP64 or 3 FP32 stage workgroups on
+// each of the 256 CUs); then halved down to FV_SMALLEST_ZCHUNK.  The other members fill the
+// GPU, so shorter chunks only repeat march starts: with chunks down to 2 or 1 planes a
+// batch of six requests took 2.97 / 3.08 against 2.91 ms.
 #ifndef FV_TARGET_WORKGROUPS
 #define FV_TARGET_WORKGROUPS 2048
 #endif
 #ifndef FV_TARGET_WORKGROUPS_F32
 #define FV_TARGET_WORKGROUPS_F32 4096
 #endif
-// z chunk of a workgroup (planes): at least FV_MIN_ZCHUNK, unless the launch would then
-// have fewer workgroups than the GPU holds at once (2 FP64 or 3 FP32 stage workgroups
-// on each of the 256 CUs); then halved down to FV_SMALLEST_ZCHUNK.  Each chunk repeats
-// the z-march's start (window loads, two z-only steps; two in-plane warm-up planes for
-// the viscous model), which costs more than idle CUs only once they are all busy.
-// Measured per stage (ms; chunk 16 / 8 / 4): NS FP64 128^3 0.318 / 0.332 / 0.355,
-// 64^3 0.225 / 0.122 / 0.075; five-equation FP32 256x64x64 0.222 / 0.143 / 0.139,
-// 128x32x32 0.222 / 0.115 / 0.064; Euler FP32 64^3 0.133 / 0.072 / 0.044.
 #ifndef FV_MIN_ZCHUNK
 #define FV_MIN_ZCHUNK 16
 #endif
 #ifndef FV_SMALLEST_ZCHUNK
 #define FV_SMALLEST_ZCHUNK 4
-#endif
-// Five-equation model, single-problem launches: chunks lengthened (never shortened) up to
-// FV_DIM_MAX_ZCHUNK planes while the launch still gives every resident workgroup slot a
-// workgroup (one round), which saves repeated march starts.  Batched members keep the
-// base chunks: with the lengthening the batched serving stream measured 1.5 % lower
-// throughput (40.2 against 40.8 requests/s), one-at-a-time solves equal.  Measured at 256x128x128 (ms per stage): FP64 with
-// 32-plane chunks (512 workgroups) 0.834 -> 0.814, characteristic 0.981 -> 0.964,
-// TENO6-A 1.417 -> 1.407, THINC 1.268 -> 1.244; FP32 with 22-plane chunks (768) 0.496 ->
-// 0.482, THINC 0.575 -> 0.562.  (NS 256^3 FP64 measured slower with longer chunks.)
-#ifndef FV_DIM_MAX_ZCHUNK
-#define FV_DIM_MAX_ZCHUNK 32
 #endif
 constexpr int RESIDENT_CUS = 256;
 
@@ -197,8 +180,40 @@ bool positivity_on(const fv_config* c)
     return c->positivity < 0 ? c->model == FV_DIM : c->positivity == 1;
 }
 
-// solo: a single-problem launch (the five-equation chunk lengthening below applies;
-// batched members keep the base chunks, which interleave better with the other members)
+// Planes per z chunk of a single-problem launch of `tiles` tile columns: the chunk with the
+// least estimated time, (planes + start) x the time per plane of a CU's fullest load.  A
+// chunk's start (window loads, z-only and warm-up steps) costs about one plane step
+// (FP32 half of one), and with n workgroups on a CU, of which S run at once (2 FP64, 3
+// FP32), a plane step of each takes f(n) times that of one alone, f(2) = 1.38 in FP64,
+// f(2) = 1.2 and f(3) = 1.6 in FP32, and full rounds of S follow each other.  The constants
+// are fitted to stage times at 120 sizes from 200x1x1 to 256^3 of the three models, each
+// with chunks of 1 to 128 planes: the estimate's choice is within 0.1 % of the fastest
+// chunk on average in FP64 and within 1 % in FP32 (longest chunks 128 and 16 planes:
+// FP32 256^3 measured 2-3 % slower with 32).  Against the rule that batched members keep, ms
+// per stage: Euler 32^3 0.037 -> 0.016, 64^3 0.041 -> 0.033, 128^3 0.191 -> 0.172; NS 176^3
+// 0.721 -> 0.658, 256^3 1.874 -> 1.832; five-equation 200^3 1.88 -> 1.56, 256^3 2.74 -> 2.60,
+// FP32 192x96x96 0.226 -> 0.169.  Results do not depend on the chunks.
+int solo_zchunk(long long tiles, int nz, bool f64)
+{
+    const int S = f64 ? 2 : 3, longest = f64 ? 128 : 16;
+    const double start = f64 ? 1.0 : 0.5;
+    const double load64[3] = {0.0, 1.0, 1.38}, load32[4] = {0.0, 1.0, 1.2, 1.6};
+    const double* load = f64 ? load64 : load32;
+    int best = 1;
+    double best_t = 0.0;
+    for (int z = 1; z <= longest && z <= nz; z++) {
+        const int chunks = (nz + z - 1) / z;
+        const long long n = (tiles * chunks + RESIDENT_CUS - 1) / RESIDENT_CUS;
+        const double t = (z + start) * ((double)(n / S) * load[S] + load[n % S]);
+        if (z == 1 || t <= best_t) {
+            best = z;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// solo: a single-problem launch (solo_zchunk; batched members take the rule above)
 template <typename Real>
 fv::StageArgs<Real> stage_args(const fv_config* c, fv::LaunchGeom& g, bool solo = false)
 {
@@ -212,23 +227,17 @@ fv::StageArgs<Real> stage_args(const fv_config* c, fv::LaunchGeom& g, bool solo 
     for (int k = 0; k < 6; k++) a.bc[k] = c->bc[k];
     a.tiles_x = (c->nx + TILE_BX - 1) / TILE_BX;
     a.tiles_y = (c->ny + TILE_BY - 1) / TILE_BY;
-    // z chunks: enough workgroups to fill 256 CUs several times over
     const long long tiles = (long long)a.tiles_x * a.tiles_y;
     const long long target = f64 ? FV_TARGET_WORKGROUPS : FV_TARGET_WORKGROUPS_F32;
     int nch = (int)((target + tiles - 1) / tiles);
     if (nch < 1) nch = 1;
     int zc = (c->nz + nch - 1) / nch;
-    if (zc < FV_MIN_ZCHUNK) {
+    if (solo) {
+        zc = solo_zchunk(tiles, c->nz, f64);
+    } else if (zc < FV_MIN_ZCHUNK) {
         zc = FV_MIN_ZCHUNK < c->nz ? FV_MIN_ZCHUNK : c->nz;
         const long long slots = (long long)RESIDENT_CUS * (f64 ? 2 : 3);
         while (zc / 2 >= FV_SMALLEST_ZCHUNK && tiles * ((c->nz + zc - 1) / zc) < slots) zc /= 2;
-    }
-    if (solo && c->model == FV_DIM) {
-        const long long slots = (long long)RESIDENT_CUS * (f64 ? 2 : 3);
-        const long long round_chunks = (slots + tiles - 1) / tiles;
-        int zl = (int)((c->nz + round_chunks - 1) / round_chunks);
-        if (zl > FV_DIM_MAX_ZCHUNK) zl = FV_DIM_MAX_ZCHUNK;
-        if (zl > zc && tiles * ((c->nz + zl - 1) / zl) >= slots) zc = zl;
     }
     a.zchunk = zc;
     a.nchunks = (c->nz + zc - 1) / zc;
