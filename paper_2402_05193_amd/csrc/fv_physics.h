@@ -92,6 +92,16 @@ __device__ __forceinline__ double sqrt_fast(double x)
 }
 __device__ __forceinline__ float sqrt_fast(float x) { return __builtin_amdgcn_sqrtf(x); }
 
+// A value the compiler does not see through: it can neither be computed ahead of this
+// point nor recognised as the same as another.  Costs no instruction; used to keep a
+// long unrolled sequence in its order where the compiler would otherwise hold more
+// intermediate results than there are registers.
+template <typename Real>
+__device__ __forceinline__ void pin(Real& x)
+{
+    asm volatile("" : "+v"(x));
+}
+
 // ---------------------------------------------------------------- EOS / maps
 template <typename Real, int MODEL>
 __device__ __forceinline__ Real density(const Real* w)
@@ -336,119 +346,116 @@ __device__ __forceinline__ void weno5z_face(const Real* v, Real eps, Real& L, Re
 // Cut-off C_T = 10^-floor(beta_bar), beta_bar = 10.5 - 3.5 (1 - g(m)),
 // g(m) = (1 - m)^4 (1 + 4 m), m = 1 - min(1, eta / 0.17), eta the smallest
 // cell indicator (|2 D- D+| + e) / (D-^2 + D+^2 + e) of cells i-1 .. i+2
-// (e = 0.9 * 0.17 * 1e-6 / (1 - 0.9 * 0.17)).  The indicator set is the same
-// for both face states.  All four indicators at or above 0.17 give m = 0 and
-// C_T = 1e-10 without a division.
+// (e = 0.9 * 0.17 * 1e-6 / (1 - 0.9 * 0.17)), D the five differences d[0..4].  The
+// indicator set is the same for both face states.  beta_bar rises with eta, so each
+// power of ten is reached at a fixed eta, (eta / 0.17)^4 (5 - 4 eta / 0.17) = 6/7, 4/7,
+// 2/7 for 10, 9, 8: the ratios are compared with those without being formed.
 template <typename Real>
-__device__ __forceinline__ Real teno6a_cutoff(Real a, Real b, Real c, Real d, Real e, Real f)
+__device__ __forceinline__ Real teno6a_cutoff(const Real* d)
 {
-    const Real cr = Real(0.17);
     const Real ee = Real(0.9 * 0.17 / (1.0 - 0.9 * 0.17) * 1e-6);
-    const Real d0 = b - a, d1 = c - b, d2 = d - c, d3 = e - d, d4 = f - e;
-    const Real n0 = fabs(Real(2) * d0 * d1) + ee, q0 = fma(d0, d0, fma(d1, d1, ee));
-    const Real n1 = fabs(Real(2) * d1 * d2) + ee, q1 = fma(d1, d1, fma(d2, d2, ee));
-    const Real n2 = fabs(Real(2) * d2 * d3) + ee, q2 = fma(d2, d2, fma(d3, d3, ee));
-    const Real n3 = fabs(Real(2) * d3 * d4) + ee, q3 = fma(d3, d3, fma(d4, d4, ee));
-    if (n0 >= cr * q0 && n1 >= cr * q1 && n2 >= cr * q2 && n3 >= cr * q3) return Real(1e-10);
-    const Real eta = fmin(fmin(n0 * rcp(q0), n1 * rcp(q1)), fmin(n2 * rcp(q2), n3 * rcp(q3)));
-    const Real m = Real(1) - fmin(Real(1), eta * Real(1.0 / 0.17));
-    const Real om = Real(1) - m, om2 = om * om;
-    const Real g = om2 * om2 * fma(Real(4), m, Real(1));
-    const Real bbar = Real(10.5) - Real(3.5) * (Real(1) - g);
-    return bbar >= Real(10) ? Real(1e-10) : bbar >= Real(9) ? Real(1e-9) : bbar >= Real(8) ? Real(1e-8) : Real(1e-7);
+    Real n[4], q[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        n[k] = fma(Real(2), fabs(d[k] * d[k + 1]), ee);
+        q[k] = fma(d[k], d[k], fma(d[k + 1], d[k + 1], ee));
+    }
+    auto reached = [&](Real eta) {
+        return (n[0] >= eta * q[0]) & (n[1] >= eta * q[1]) & (n[2] >= eta * q[2]) & (n[3] >= eta * q[3]);
+    };
+    if (reached(Real(0.14656513787745196))) return Real(1e-10);
+    return reached(Real(0.12253846143808744)) ? Real(1e-9) : reached(Real(0.09674941399607152)) ? Real(1e-8) : Real(1e-7);
 }
 
-// Left-biased TENO6-A value at x_{i+1/2} from v_{i-2..i+3} = a..f (the right
-// state of the face is the same function of the mirrored stencil).
-//  * Jiang-Shu smoothness indicators beta_0..beta_3 of the candidates and
-//    beta_6 of the six-cell polynomial, over cell i; the 4- and 6-cell ones
-//    are written with values relative to v_i (they see differences only), so
-//    their rounding scales with the data's variation, not its magnitude.
+// The TENO6-A value at the + face of a cell of value v from the five differences
+// d1 .. d5 of its stencil v_{i-2..i+3}, their differences t1 .. t4, the curvature terms
+// c1 .. c3 = 13/12 t_k^2 + eps and b6 = beta_6 + eps; the - face of the next cell is the
+// mirror image.
+//  * Jiang-Shu smoothness indicators of the candidates over cell i as sums of squares:
+//    beta_0..2 as in WENO5-Z, and with s = t4 - t3 (the four-cell candidate's third
+//    difference) beta_3 = (d3 - t3/2 + s/3)^2 + 13/12 (t3 - s)^2 + 781/720 s^2.
 //  * tau_6 = |beta_6 - (beta_0 + 4 beta_1 + beta_2) / 6|.
 //  * stencil k is dropped when gamma_k / sum gamma < C_T, gamma_k =
-//    (1 + tau_6 / (beta_k + eps))^6; evaluated as s_k^6 < C_T sum s^6 with
-//    s_k = gamma_k^(1/6) / max gamma^(1/6) = A + A tau_6 / (beta_k + eps),
-//    A = e_min / (e_min + tau_6), which stays finite where gamma overflows
-//    (FP32: A + C e_min / e_k with C = tau_6 / (e_min + tau_6), the same value,
-//    which keeps s = 1 for the smoothest candidate where A underflows).
-//  * kept stencils combine with the linear weights (1, 9, 6, 4) / 20.
+//    (1 + tau_6 / e_k)^6, e_k = beta_k + eps; evaluated as s_k^6 < C_T sum s^6 with
+//    s_k = gamma_k^(1/6) over its largest, which stays finite where gamma overflows.
+//    FP64: s_k from (e_k + tau) prod_{j != k} e_j, one reciprocal.  FP32, where those
+//    products leave the range: A + C e_min / e_k with A = e_min / (e_min + tau_6), C =
+//    tau_6 / (e_min + tau_6), which keeps s = 1 for the smoothest candidate where A
+//    underflows.
+//  * kept stencils combine with the linear weights (1, 9, 6, 4) / 20; candidate values
+//    are increments over v.
 template <typename Real>
-__device__ __forceinline__ Real teno6a_one(Real a, Real b, Real c, Real d, Real e, Real f, Real eps, Real ct)
+__device__ __forceinline__ Real teno6a_value(Real v, Real d1, Real d2, Real d3, Real d4, Real d5, Real t1, Real t3,
+                                             Real t4, Real c1, Real c2, Real c3, Real b6, Real eps, Real ct)
 {
-    const Real k13 = Real(13.0 / 12.0), q = Real(0.25);
-    const Real t0 = a - Real(2) * b + c, s0 = a - Real(4) * b + Real(3) * c;
-    const Real t1 = b - Real(2) * c + d, s1 = b - d;
-    const Real t2 = c - Real(2) * d + e, s2 = Real(3) * c - Real(4) * d + e;
-    const Real b0 = k13 * t0 * t0 + q * s0 * s0;
-    const Real b1 = k13 * t1 * t1 + q * s1 * s1;
-    const Real b2 = k13 * t2 * t2 + q * s2 * s2;
-    const Real A = a - c, B = b - c, D = d - c, E = e - c, F = f - c;
-    const Real b3 = (D * (Real(11003) * D - Real(17246) * E + Real(4642) * F) + E * (Real(7043) * E - Real(3882) * F) +
-                     Real(547) * F * F) *
-                    Real(1.0 / 240.0);
-    const Real b6 = (A * (Real(271779) * A - Real(2380800) * B - Real(3462252) * D + Real(1458762) * E -
-                          Real(245620) * F) +
-                     B * (Real(5653317) * B + Real(17905032) * D - Real(7727988) * E + Real(1325006) * F) +
-                     D * (Real(17195652) * D - Real(15880404) * E + Real(2863984) * F) +
-                     E * (Real(3824847) * E - Real(1429976) * F) + Real(139633) * F * F) *
-                    Real(1.0 / 120960.0);
-    const Real tau = fabs(b6 - (b0 + Real(4) * b1 + b2) * Real(1.0 / 6.0));
-    const Real e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps, e3 = b3 + eps;
-    Real r0, r1, r2, r3;
-    if constexpr (sizeof(Real) == 8) {
-        const Real p01 = e0 * e1, p23 = e2 * e3;
-        const Real R = rcp(p01 * p23);
-        const Real u = p23 * R, v = p01 * R;
-        r0 = e1 * u;
-        r1 = e0 * u;
-        r2 = e3 * v;
-        r3 = e2 * v;
-    } else {
-        r0 = rcp(e0);
-        r1 = rcp(e1);
-        r2 = rcp(e2);
-        r3 = rcp(e3);
-    }
-    const Real em = fmin(fmin(e0, e1), fmin(e2, e3));
-    auto pow6 = [](Real x) {
-        const Real x2 = x * x;
-        return x2 * x2 * x2;
+    const Real h0 = fma(Real(0.5), t1, d2), h2 = fma(Real(-0.5), t3, d3), x = d2 + d3;
+    const Real e0 = fma(h0, h0, c1), e1 = fma(Real(0.25) * x, x, c2), e2 = fma(h2, h2, c3);
+    const Real s = t4 - t3, w = t3 - s, h3 = fma(Real(1.0 / 3.0), s, h2);
+    const Real e3 = fma(h3, h3, fma(Real(13.0 / 12.0) * w, w, fma(Real(781.0 / 720.0) * s, s, eps)));
+    const Real tau = fabs(fma(Real(-1.0 / 6.0), fma(Real(4), e1, e0 + e2), b6));
+    auto pow6 = [](Real y) {
+        const Real y2 = y * y;
+        return y2 * y2 * y2;
     };
     Real g0, g1, g2, g3;
     if constexpr (sizeof(Real) == 8) {
-        const Real An = em * rcp(em + tau), Bn = An * tau;
-        g0 = pow6(fma(Bn, r0, An));
-        g1 = pow6(fma(Bn, r1, An));
-        g2 = pow6(fma(Bn, r2, An));
-        g3 = pow6(fma(Bn, r3, An));
+        const Real p01 = e0 * e1, p23 = e2 * e3, p = p01 * p23;
+        const Real n0 = fma(tau, e1 * p23, p), n1 = fma(tau, e0 * p23, p);
+        const Real n2 = fma(tau, e3 * p01, p), n3 = fma(tau, e2 * p01, p);
+        const Real R = rcp(fmax(fmax(n0, n1), fmax(n2, n3)));
+        g0 = pow6(n0 * R);
+        g1 = pow6(n1 * R);
+        g2 = pow6(n2 * R);
+        g3 = pow6(n3 * R);
     } else {
+        const Real em = fmin(fmin(e0, e1), fmin(e2, e3));
         const Real inv = rcp(em + tau);
         const Real An = em * inv, Cm = em * (tau * inv);
-        g0 = pow6(fma(Cm, r0, An));
-        g1 = pow6(fma(Cm, r1, An));
-        g2 = pow6(fma(Cm, r2, An));
-        g3 = pow6(fma(Cm, r3, An));
+        g0 = pow6(fma(Cm, rcp(e0), An));
+        g1 = pow6(fma(Cm, rcp(e1), An));
+        g2 = pow6(fma(Cm, rcp(e2), An));
+        g3 = pow6(fma(Cm, rcp(e3), An));
     }
-    const Real thr = ct * (g0 + g1 + g2 + g3);
+    const Real thr = ct * ((g0 + g1) + (g2 + g3));
     const Real w0 = g0 >= thr ? Real(1) : Real(0), w1 = g1 >= thr ? Real(9) : Real(0);
     const Real w2 = g2 >= thr ? Real(6) : Real(0), w3 = g3 >= thr ? Real(4) : Real(0);
-    // candidates: 6 p_0..2 and 12 p_3
-    const Real p0 = Real(2) * a - Real(7) * b + Real(11) * c;
-    const Real p1 = -b + Real(5) * c + Real(2) * d;
-    const Real p2 = Real(2) * c + Real(5) * d - e;
-    const Real p3 = Real(3) * c + Real(13) * d - Real(5) * e + f;
-    const Real num = Real(2) * (w0 * p0 + w1 * p1 + w2 * p2) + w3 * p3;
-    return num * rcp(Real(12) * (w0 + w1 + w2 + w3));
+    // candidate increments times 6
+    const Real y = Real(2) * d3;
+    const Real q0 = fma(Real(5), d2, Real(-2) * d1), q1 = y + d2, q2 = fma(Real(2), y, -d4);
+    const Real q3 = fma(Real(4.5), d3, fma(Real(0.5), d5, Real(-2) * d4));
+    const Real n = fma(w0, q0, fma(w1, q1, fma(w2, q2, w3 * q3)));
+    return fma(n, rcp(Real(6) * ((w0 + w1) + (w2 + w3))), v);
 }
 
-// Both TENO6-A states of the face between cells i and i+1 from v_{i-2..i+3}.
+// Both TENO6-A states of the face between cells i and i+1 from v_{i-2..i+3} = a .. f.
+// beta_6 (the indicator of the six-cell polynomial over cell i, or i+1 for the mirrored
+// side) splits into a part even under the mirror and one that changes sign; in terms of
+// the face-centred differences u1, u3, u5 (odd) and v2, v4 (even) the two sides are X + Y
+// and X - Y, formed together.
 template <typename Real>
 __device__ __forceinline__ void teno6a_pair(Real a, Real b, Real c, Real d, Real e, Real f, Real eps, Real& vl,
                                             Real& vr)
 {
-    const Real ct = teno6a_cutoff(a, b, c, d, e, f);
-    vl = teno6a_one(a, b, c, d, e, f, eps, ct);
-    vr = teno6a_one(f, e, d, c, b, a, eps, ct);
+    const Real dd[5] = {b - a, c - b, d - c, e - d, f - e};
+    Real t[4], cv[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        t[k] = dd[k + 1] - dd[k];
+        cv[k] = weno5z_curvature(t[k], eps);
+    }
+    const Real u1 = dd[2], u3 = t[2] - t[1], u5 = fma(Real(-3), u3, t[3] - t[0]);
+    const Real v2 = t[1] + t[2], v4 = (t[0] + t[3]) - v2;
+    const Real X = fma(fma(Real(-1.0 / 60.0), u5, fma(Real(1.0 / 6.0), u3, u1)), u1,
+                       fma(fma(Real(-757.0 / 15120.0), u5, Real(109.0 / 80.0) * u3), u3,
+                           fma(Real(82129.0 / 60480.0) * u5, u5,
+                               fma(fma(Real(-1.0 / 15.0), v4, Real(1.0 / 3.0) * v2), v2,
+                                   fma(Real(1727.0 / 5040.0) * v4, v4, eps)))));
+    const Real Y = fma(fma(Real(1.0 / 12.0), v4, Real(-0.5) * v2), u1,
+                       fma(fma(Real(-47.0 / 96.0), v4, Real(-7.0 / 12.0) * v2), u3,
+                           fma(Real(-9439.0 / 17280.0), v4, Real(0.05) * v2) * u5));
+    const Real ct = teno6a_cutoff(dd);
+    vl = teno6a_value(c, dd[0], dd[1], dd[2], dd[3], dd[4], t[0], t[2], t[3], cv[0], cv[1], cv[2], X + Y, eps, ct);
+    vr = teno6a_value(d, -dd[4], -dd[3], -dd[2], -dd[1], -dd[0], t[3], t[1], t[0], cv[3], cv[2], cv[1], X - Y, eps, ct);
 }
 
 // Face states by WENO5-Z or TENO6-A of characteristic variables (Sec. 3.2 steps 1-4 and
@@ -486,6 +493,14 @@ __device__ __forceinline__ void char_face_states(const Material<Real>& mat, Sten
             teno6a_pair(q[0], q[1], q[2], q[3], q[4], q[5], eps, L, R);
         } else {
             weno5z_face(q, eps, L, R);
+        }
+        // one field after the other (five-equation FP64 WENO5-Z 80 -> 12 spilled VGPRs,
+        // 706 -> 614 us per step at 160x80x80; TENO6-A with THINC 325 -> 113, 2207 ->
+        // 1571 us).  Without spills to avoid, the single-phase FP64 WENO5-Z kernels lost
+        // 2 % with it.
+        if constexpr (MODEL == DIM || TENO || sizeof(Real) == 4) {
+            pin(L);
+            pin(R);
         }
     };
     Real amL, amR, apL, apR;

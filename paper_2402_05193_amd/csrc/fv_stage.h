@@ -125,7 +125,7 @@ __device__ __forceinline__ double inverse_dt(const StageArgs<Real>& a, const Rea
 // t), b fastest across the lanes.  The position is advanced by NT without divisions
 // (b from a 24-bit multiply); the loop stays rolled for its registers.
 template <int NB, int NA, int NC, int NT, typename Item>
-__device__ __forceinline__ void pair_items(int t, Item item)
+__device__ __forceinline__ void list_items(int t, Item item)
 {
     constexpr int N = NA * NB;                 // positions per component
     constexpr int SM = NT / N, ST = NT % N;    // one stride of NT
@@ -363,10 +363,9 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         // not see through: otherwise it computes the index arithmetic of every phase once
         // and holds it in registers across the plane loop.  NS FP64 56 -> 0 spilled VGPRs,
         // FP32 16 -> 0 (168 -> 139 VGPRs), five-equation FP64 84 -> 70; per stage NS 256^3
-        // 2.40 -> 2.06 ms, five-equation THINC FP32 192x96x96 0.33 -> 0.30.  The TENO6-A
-        // kernels measured 1-2 % slower with it.
+        // 2.40 -> 2.06 ms, five-equation THINC FP32 192x96x96 0.33 -> 0.30
         int tid = threadIdx.x;
-        if constexpr (!TENO) asm volatile("" : "+v"(tid));
+                pin(tid);
         const bool has_cell = tid < NCELL;
         const int tx = tid % BX, ty = has_cell ? tid / BX : 0;
         // task lists have a few tasks more than threads; the wave that takes the
@@ -662,10 +661,23 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // primitive variables: the reconstruction of cell s-1 from W(s-3 .. s+1) gives
             // its face values at s-3/2 (used now) and s-1/2 (carried to the next step)
             Real vm_new[NC], vp[NC];
+            // one component after the other where the registers are short of the interleaved
+            // form: five-equation FP64 (64 -> 18 spilled VGPRs, 2.08 -> 1.86 ms per step at
+            // 256x128x128) and THINC FP32 (0.688 -> 0.672 ms at 192x96x96), and where a fourth
+            // workgroup fits a CU (single phase FP32, 138 -> 116 VGPRs: NS 256^3 3.61 -> 3.22
+            // ms, Euler 2.27 -> 2.20).  Elsewhere it costs 1-3 % (NS FP64, the limited FP32
+            // kernels).
+            constexpr bool Z_IN_ORDER =
+                sizeof(Real) == 8 ? MODEL == DIM : (THINC || (MODEL != DIM && POS == 0));
             if constexpr (!FACE) {
 #pragma unroll
-                for (int m = 0; m < NC; m++)
+                for (int m = 0; m < NC; m++) {
                     weno5z_pair(win[0][m], win[1][m], win[2][m], win[3][m], win[4][m], weps, vm_new[m], vp[m]);
+                    if constexpr (Z_IN_ORDER) {
+                        pin(vm_new[m]);
+                        pin(vp[m]);
+                    }
+                }
             }
             if (s >= z0 + 1) {
                 // z face s-3/2 between cells s-2 (win[1]) and s-1 (win[2])
@@ -701,8 +713,11 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     char_face_states<Real, MODEL, 2, TENO>(mat, [&](int q, int m) { return win[q][m]; }, weps, wl, wr);
                 } else if constexpr (TENO) {
 #pragma unroll
-                    for (int m = 0; m < NC; m++)
+                    for (int m = 0; m < NC; m++) {
                         teno6a_pair(win[0][m], win[1][m], win[2][m], win[3][m], win[4][m], win[5][m], weps, wl[m], wr[m]);
+                        pin(wl[m]);  // one component after the other: 298 -> 39 spilled VGPRs
+                        pin(wr[m]);  // (five-equation FP64, 1523 -> 916 us per step at 160x80x80)
+                    }
                 } else {
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
@@ -829,16 +844,14 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 }
             } else if constexpr (TENO) {
                 // one item = one component of one x face (faces between cells f-1 and f)
-                for (int it = rt; it < NC * TL::NFX; it += NT) {
-                    const int m = it / TL::NFX, t = it - m * TL::NFX;
-                    const int j = t / (BX + 1), f = t - j * (BX + 1);
+                list_items<BX + 1, BY, NC, NT>(rt, [&](int m, int j, int f) {
                     const Real* c = &wp(m, f - 3, j);
                     const int e = m * FSZ + j * FRX + f;
                     teno6a_pair(c[0], c[1], c[2], c[3], c[4], c[5], weps, FL[e], FR[e + 1]);
-                }
+                });
             } else {
                 // one item = one component of two neighbouring cells 2q-1, 2q of a row
-                pair_items<(BX + 2) / 2, BY, NC, NT>(rt, [&](int m, int j, int q) {
+                list_items<(BX + 2) / 2, BY, NC, NT>(rt, [&](int m, int j, int q) {
                     const Real* c = &Wp[m * PLANE + (j + 3) * PX + 2 * q];
                     const Real v[6] = {c[0], c[1], c[2], c[3], c[4], c[5]};
                     Real vm[2], vp[2];
@@ -967,16 +980,14 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 }
             } else if constexpr (TENO) {
                 // one item = one component of one y face (faces between rows f-1 and f)
-                for (int it = rt; it < NC * TL::NFY; it += NT) {
-                    const int m = it / TL::NFY, t = it - m * TL::NFY;
-                    const int f = t / BX, i = t - f * BX;
+                list_items<BX, BY + 1, NC, NT>(rt, [&](int m, int f, int i) {
                     const Real* c = &wp(m, i, f - 3);
-                    teno6a_pair(c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX], weps, GL[m * FSZ + t],
-                                GR[m * FSZ + t + BX]);
-                }
+                    const int e = m * FSZ + f * BX + i;
+                    teno6a_pair(c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX], weps, GL[e], GR[e + BX]);
+                });
             } else {
                 // one item = one component of two neighbouring cells 2q-1, 2q of a column
-                pair_items<BX, (BY + 2) / 2, NC, NT>(rt, [&](int m, int q, int i) {
+                list_items<BX, (BY + 2) / 2, NC, NT>(rt, [&](int m, int q, int i) {
                     const Real* c = &Wp[m * PLANE + 2 * q * PX + i + 3];
                     const Real v[6] = {c[0], c[PX], c[2 * PX], c[3 * PX], c[4 * PX], c[5 * PX]};
                     Real vm[2], vp[2];
@@ -1123,7 +1134,13 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
 #pragma unroll
         for (int q = 0; q < NWIN - 1; q++)
 #pragma unroll
-            for (int f = 0; f < NC; f++) win[q][f] = win[q + 1][f];
+            for (int f = 0; f < NC; f++) {
+                win[q][f] = win[q + 1][f];
+                // otherwise the compiler carries the differences that the next step's z
+                // reconstruction shares with this one's in registers (five-equation
+                // THINC FP64 133 -> 113 spilled VGPRs, 1016 -> 956 us per step at 160x80x80)
+                pin(win[q][f]);
+            }
         if constexpr (THINC) {
 #pragma unroll
             for (int q = 0; q < NWIN - 1; q++) psw[q] = psw[q + 1];
