@@ -195,7 +195,8 @@ struct Tile {
 };
 
 // One workgroup of the fused stage: tile column `bid` of the problem described by `a`.
-template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH>
+// FLAT: for grids of one cell along y or z (see one_cell_axis).
+template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH, bool FLAT = false>
 __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int bid, unsigned char* smem_raw)
 {
     using L = Layout<MODEL>;
@@ -282,9 +283,22 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     Real win[NWIN][NC];
     // THINC: psi of the window's volume fractions (thinc_psi), computed once per plane
     Real psw[THINC ? NWIN : 1];
+    // FLAT, axes of one cell: both faces of a cell see the same stencil and their fluxes
+    // cancel exactly, so the y phases or the z faces are left out; a cell whose own flux
+    // would not be a number keeps that in its result (one_cell_axis).  y: the rows of the
+    // tile beyond the only one are left out of the x phases too.  z: one plane step and the
+    // finalisation.  What bounds these launches is the latency of one workgroup's march:
+    // per stage a tube of 200 cells 24 -> 10 us (five-equation FP64), 150x150x1 16 -> 13 us
+    // (Euler FP64).  A kernel of its own: as a run-time switch it made the large grids 3-4 %
+    // slower.
+    static_assert(!(FLAT && REC_FLAGS), "the kernel that records limiter decisions does every face");
+    const bool one_y = FLAT && a.ny == 1, one_z = FLAT && a.nz == 1;
+    auto one_cell_axis = [&](const Real* w) {
+        return density<Real, MODEL>(w) > Real(0) && rhoc2<Real, MODEL>(mat, w) > Real(0) ? Real(0) : Real(NAN);
+    };
     // viscous: two warm-up planes for the in-plane derivatives of the first z faces;
     // THINC: one, for the in-plane volume-fraction gradient of cell z0-1
-    const int s_begin = VISC ? z0 - 2 : (THINC ? z0 - 1 : z0);
+    const int s_begin = one_z ? z0 : (VISC ? z0 - 2 : (THINC ? z0 - 1 : z0));
 #pragma unroll
     for (int q = 0; q < NWIN - 1; q++) {
         if (has_cell) load_w(gx, gy, s_begin - 3 - WO + q, win[q]);
@@ -358,7 +372,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         PSQ[(s_begin & 1) * TL::NRING + rh] = thinc_psi(ring_alpha(s_begin));
     }
 
-    for (int s = s_begin; s <= z1 + 1; s++) {
+    for (int s = s_begin; s <= z1 + 1; s += one_z ? 2 : 1) {
         // the thread's indices formed anew in every step from a copy that the compiler does
         // not see through: otherwise it computes the index arithmetic of every phase once
         // and holds it in registers across the plane loop.  NS FP64 56 -> 0 spilled VGPRs,
@@ -406,7 +420,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         if constexpr (!LATE_OWN && !OWN_AFTER_Z) load_own();
         const bool xy = (s >= z0) && (s < z1);
         // THINC also stages plane z1 (the cell above the last z face of the chunk)
-        const bool need_plane = xy || (VISC && s >= z0 - 2) || (THINC && s >= z0 - 1 && s <= z1);
+        const bool need_plane =
+            xy || (!one_z && ((VISC && s >= z0 - 2) || (THINC && s >= z0 - 1 && s <= z1)));
         Real accC[NC];
         Real srcC = 0;
         Real Dnew[4] = {0, 0, 0, 0};
@@ -661,6 +676,10 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // primitive variables: the reconstruction of cell s-1 from W(s-3 .. s+1) gives
             // its face values at s-3/2 (used now) and s-1/2 (carried to the next step)
             Real vm_new[NC], vp[NC];
+            if (one_z) {
+#pragma unroll
+                for (int m = 0; m < NC; m++) vm_new[m] = vp[m] = Real(0);
+            }
             // one component after the other where the registers are short of the interleaved
             // form: five-equation FP64 (64 -> 18 spilled VGPRs, 2.08 -> 1.86 ms per step at
             // 256x128x128) and THINC FP32 (0.688 -> 0.672 ms at 192x96x96), and where a fourth
@@ -669,7 +688,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // kernels).
             constexpr bool Z_IN_ORDER =
                 sizeof(Real) == 8 ? MODEL == DIM : (THINC || (MODEL != DIM && POS == 0));
-            if constexpr (!FACE) {
+            if (!FACE && !one_z) {
 #pragma unroll
                 for (int m = 0; m < NC; m++) {
                     weno5z_pair(win[0][m], win[1][m], win[2][m], win[3][m], win[4][m], weps, vm_new[m], vp[m]);
@@ -682,6 +701,13 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             if (s >= z0 + 1) {
                 // z face s-3/2 between cells s-2 (win[1]) and s-1 (win[2])
                 Real Fd[4];
+                Real wl[NC], wr[NC], F[NC], uh;
+                if (one_z) {
+                    uh = Real(0);
+                    F[0] = one_cell_axis(win[1 + WO]);
+#pragma unroll
+                    for (int m = 1; m < NC; m++) F[m] = F[0];
+                } else {
                 if constexpr (VISC) {
                     // viscous part first: its inputs are the window and the carried derivatives
                     const Real i24 = a.inv24dz;
@@ -707,7 +733,6 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     viscous_flux_from_gradients<Real, 2>(dn, vf, g_xw, g_yw, g_xu, g_yv, muf, kf, Fd);
                     __builtin_amdgcn_sched_barrier(0);  // keep the two flux parts from interleaving (registers)
                 }
-                Real wl[NC], wr[NC], F[NC], uh;
                 if constexpr (CHARV) {
                     // characteristic variables of the face's frozen state, stencil s-4 .. s+1
                     char_face_states<Real, MODEL, 2, TENO>(mat, [&](int q, int m) { return win[q][m]; }, weps, wl, wr);
@@ -762,6 +787,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     F[V + 1] -= Fd[1];
                     F[V + 2] -= Fd[2];
                     F[P] -= Fd[3];
+                }
                 }
                 if (s >= z0 + 2 && own_valid) {
                     // finalise cell s-2: R = (x/y part) - (F_{s-3/2} - F_{s-5/2}) / dz
@@ -851,7 +877,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 });
             } else {
                 // one item = one component of two neighbouring cells 2q-1, 2q of a row
-                list_items<(BX + 2) / 2, BY, NC, NT>(rt, [&](int m, int j, int q) {
+                auto item = [&](int m, int j, int q) {
                     const Real* c = &Wp[m * PLANE + (j + 3) * PX + 2 * q];
                     const Real v[6] = {c[0], c[1], c[2], c[3], c[4], c[5]};
                     Real vm[2], vp[2];
@@ -861,7 +887,9 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     FL[e + 1] = vm[1];
                     FR[e] = vp[0];
                     FR[e + 1] = vp[1];
-                });
+                };
+                if (one_y) list_items<(BX + 2) / 2, 1, NC, NT>(tid, item);
+                else list_items<(BX + 2) / 2, BY, NC, NT>(rt, item);
             }
             if constexpr (VISC) {
                 // d/dy of u (c = 0) and v (c = 1) on the x-face region
@@ -878,7 +906,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // the wave holding rt = 0 also runs the remainder round of the x and y face lists
             const bool prio_tail = sizeof(Real) == 8 && (rt >> 6) == 0;  // wave-uniform
             if (prio_tail) __builtin_amdgcn_s_setprio(2);
-            for (int t = rt; t < TL::NFX; t += NT) {
+            for (int t = one_y ? tid : rt; t < (one_y ? BX + 1 : TL::NFX); t += NT) {
                 const int j = t / (BX + 1), f = t % (BX + 1);
                 const int e = j * FRX + f;
                 Real wl[NC], wr[NC], F[NC], uh;
@@ -960,8 +988,17 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                     else accC[m] = v;
                 }
                 if constexpr (MODEL == DIM) srcC = (UHB[fl + 1] - UHB[fl]) * idx;
+                if (one_y) {
+                    const Real d = one_cell_axis(win[3 + WO]);
+#pragma unroll
+                    for (int m = 0; m < NC; m++) {
+                        if constexpr (ACC_LDS) slot[m * NCELL] -= d;
+                        else accC[m] -= d;
+                    }
+                }
             }
             __syncthreads();
+            if (!one_y) {
             // ---- P4: y reconstructions (rows -1 .. BY of each column) [+ d/dx on the y region]
             if (prio_p4) __builtin_amdgcn_s_setprio(1);
             Real* GL = FB;
@@ -1095,6 +1132,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 }
                 if constexpr (MODEL == DIM) srcC += (UHB[fl + BX] - UHB[fl]) * idy;
             }
+            }
         }
         // rotate carries
         if constexpr (ACC_HALF) {
@@ -1113,7 +1151,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 accB[m] = accC[m];
             }
         }
-        srcA = srcB;
+        srcA = one_z ? srcC : srcB;
         srcB = srcC;
         if constexpr (VISC) {
 #pragma unroll
@@ -1180,6 +1218,15 @@ __global__ void __launch_bounds__(NTH, stage_waves<Real>()) stage_kernel(const S
     stage_body<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>(*pa, (int)blockIdx.x, smem_raw);
 }
 
+// The same for grids of one cell along y or z
+template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH>
+__global__ void __launch_bounds__(NTH, stage_waves<Real>()) flat_stage_kernel(const StageArgs<Real> a)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const StageArgs<Real>* pa = (const StageArgs<Real>*)__builtin_amdgcn_kernarg_segment_ptr();
+    stage_body<Real, MODEL, POS, REC, VMODE, BX, BY, NTH, true>(*pa, (int)blockIdx.x, smem_raw);
+}
+
 // Many independent problems in one launch: the workgroups of problem r are
 // first[r] .. first[r+1]-1; args[r] describes problem r (same model, precision,
 // limiter setting, reconstruction family and viscosity / interface variant for every
@@ -1209,27 +1256,36 @@ __global__ void __launch_bounds__(NTH, stage_waves<Real>())
 }
 
 // ------------------------------------------------------------------ launchers
-template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH>
+template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH, bool FLAT = false>
 static hipError_t launch_tile(const StageArgs<Real>& args, const LaunchGeom& g, hipStream_t st)
 {
     using TL = Tile<Real, MODEL, BX, BY, NTH, MODEL == NS && VMODE != VM_EXT && VMODE != VM_EXT_LAW,
                     MODEL == DIM && VMODE == XM_THINC>;
     const size_t lds = TL::bytes();
+    void (*k)(const StageArgs<Real>);
+    if constexpr (FLAT) k = flat_stage_kernel<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>;
+    else k = stage_kernel<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)stage_kernel<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((stage_kernel<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>), dim3(g.nblocks), dim3(NTH), lds,
-                       st, args);
+    hipLaunchKernelGGL(k, dim3(g.nblocks), dim3(NTH), lds, st, args);
     return hipGetLastError();
 }
 
 template <typename Real, int MODEL, int REC, int VMODE>
 static hipError_t launch_pos(const StageArgs<Real>& args, const LaunchGeom& g, hipStream_t st)
 {
+    // one- and two-dimensional problems (not the face-based reconstructions, whose general
+    // kernels take them: each variant is one more kernel in the library)
+    if constexpr (REC == REC_WENO_PRIM) {
+        if (!args.flags && (args.ny == 1 || args.nz == 1))
+            return args.positivity
+                       ? launch_tile<Real, MODEL, 1, REC, VMODE, TILE_BX, TILE_BY, TILE_NT, true>(args, g, st)
+                       : launch_tile<Real, MODEL, 0, REC, VMODE, TILE_BX, TILE_BY, TILE_NT, true>(args, g, st);
+    }
     if (args.positivity) {
         if (args.flags) return launch_tile<Real, MODEL, 2, REC, VMODE, TILE_BX, TILE_BY, TILE_NT>(args, g, st);
         return launch_tile<Real, MODEL, 1, REC, VMODE, TILE_BX, TILE_BY, TILE_NT>(args, g, st);
