@@ -576,8 +576,8 @@ int compute_dt(const fv_config* cfg, const void* U, double* dt_dev, void* ws, vo
     const fv::AuxArgs a = aux_args(cfg);
     const double mu = cfg->model == FV_NS ? cfg->mu : 0.0;
     hipError_t e = cfg->dtype == FV_F64
-                       ? fv::launch_dt<double>(a, (const double*)U, mu, cfg->cfl, w.inv_max, dt_dev, nullptr, (hipStream_t)stream)
-                       : fv::launch_dt<float>(a, (const float*)U, mu, cfg->cfl, w.inv_max, dt_dev, nullptr, (hipStream_t)stream);
+                       ? fv::launch_dt<double>(a, (const double*)U, mu, cfg->cfl, w.inv_max, dt_dev, (hipStream_t)stream)
+                       : fv::launch_dt<float>(a, (const float*)U, mu, cfg->cfl, w.inv_max, dt_dev, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "compute_dt");
     return FV_OK;
 }
@@ -599,8 +599,8 @@ static int advance_impl(const fv_config* cfg, void* U, int32_t nsteps, double dt
         // dt of the first step from a full reduction; every later dt comes from the
         // reduction fused into the previous step's third stage
         hipError_t e = cfg->dtype == FV_F64
-                           ? fv::launch_dt<double>(a, (const double*)U, mu, cfg->cfl, w.inv_max, w.dt, nullptr, st)
-                           : fv::launch_dt<float>(a, (const float*)U, mu, cfg->cfl, w.inv_max, w.dt, nullptr, st);
+                           ? fv::launch_dt<double>(a, (const double*)U, mu, cfg->cfl, w.inv_max, w.dt, st)
+                           : fv::launch_dt<float>(a, (const float*)U, mu, cfg->cfl, w.inv_max, w.dt, st);
         if (e != hipSuccess) return hip_fail(e, "advance: dt");
     }
     for (int n = 0; n < nsteps; n++) {
@@ -1106,6 +1106,7 @@ int batch_set(fv_batch* b, int32_t n, const fv_config* cfgs, void* const* U, voi
     char* img = b->host[k];
     memset(img, 0, end);
     std::vector<int> slot(groups.size(), 0), first(groups.size(), 0);
+    bool starts = false;
     fv::BatchScalars* sc = reinterpret_cast<fv::BatchScalars*>(img + scal_off);
     for (int i = 0; i < n; i++) {
         const int p = pos_of[gid[i]];
@@ -1120,6 +1121,8 @@ int batch_set(fv_batch* b, int32_t n, const fv_config* cfgs, void* const* U, voi
         sc[i].dt = w.dt;
         sc[i].t_acc = w.t_acc;
         sc[i].cfl = cfgs[i].cfl;
+        sc[i].fresh = fresh && fresh[i] ? 1 : 0;
+        starts = starts || sc[i].fresh;
     }
     for (size_t p = 0; p < groups.size(); p++) {
         reinterpret_cast<int*>(img + groups[p].hdr_off)[0] = groups[p].count;
@@ -1147,16 +1150,26 @@ int batch_set(fv_batch* b, int32_t n, const fv_config* cfgs, void* const* U, voi
     if (e != hipSuccess) return hip_fail(e, "batch_set: table upload");
     b->pending[k] = true;
     b->cur = 1 - k;
-    // new members: first dt from a full reduction, simulated time 0
+    // new members: first dt from a full reduction, simulated time 0 (their words set by one
+    // launch before and one after the members' reductions)
+    const fv::BatchScalars* scal = reinterpret_cast<const fv::BatchScalars*>(b->table + scal_off);
+    const int* nmem = reinterpret_cast<const int*>(b->table + scal_hdr_off);
+    if (starts) {
+        e = fv::launch_batch_fresh(scal, nmem, n, true, st);
+        if (e != hipSuccess) return hip_fail(e, "batch_set: first dt");
+    }
     for (int i = 0; i < n; i++) {
         if (!fresh || !fresh[i]) continue;
         const fv_config* c = &cfgs[i];
         const WsLayout w = ws_layout(c, ws[i]);
         const fv::AuxArgs a = aux_args(c);
         const double mu = c->model == FV_NS ? c->mu : 0.0;
-        e = c->dtype == FV_F64 ? fv::launch_dt<double>(a, (const double*)U[i], mu, c->cfl, w.inv_max, w.dt, nullptr, st)
-                               : fv::launch_dt<float>(a, (const float*)U[i], mu, c->cfl, w.inv_max, w.dt, nullptr, st);
-        if (e == hipSuccess) e = fv::launch_reset_max((unsigned long long*)w.t_acc, st);
+        e = c->dtype == FV_F64 ? fv::launch_inv_dt<double>(a, (const double*)U[i], mu, w.inv_max, st)
+                               : fv::launch_inv_dt<float>(a, (const float*)U[i], mu, w.inv_max, st);
+        if (e != hipSuccess) return hip_fail(e, "batch_set: first dt");
+    }
+    if (starts) {
+        e = fv::launch_batch_fresh(scal, nmem, n, false, st);
         if (e != hipSuccess) return hip_fail(e, "batch_set: first dt");
     }
     b->groups = groups;

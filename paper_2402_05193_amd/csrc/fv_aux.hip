@@ -217,42 +217,57 @@ template hipError_t launch_init<double>(const AuxArgs&, int, const double*, int,
 template hipError_t launch_init<float>(const AuxArgs&, int, const double*, int, uint64_t, float*, hipStream_t);
 
 // ------------------------------------------------------------------ CFL time step
-__global__ void add_scalar_kernel_fwd(double* t_acc, const double* dt)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *t_acc += *dt;
-}
-
-__global__ void reset_u64_kernel(unsigned long long* p)
+__global__ void reset_max_kernel(unsigned long long* p)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0ull;
 }
 
+// inverse CFL time step of one cell
 template <typename Real, int MODEL>
+__device__ __forceinline__ double cell_inverse_dt(const AuxArgs& a, const Real* u, double mu, const double* ih, double kv)
+{
+    constexpr int NC = Layout<MODEL>::NC, V = Layout<MODEL>::V;
+    Real w[NC];
+    cons_to_prim<Real, MODEL>(mat_of<Real>(a), u, w);
+    const double rho = (double)density<Real, MODEL>(w);
+    const double c = sqrt((double)rhoc2<Real, MODEL>(mat_of<Real>(a), w) / rho);
+    double t = fmax((fabs((double)w[V]) + c) * ih[0],
+                    fmax((fabs((double)w[V + 1]) + c) * ih[1], (fabs((double)w[V + 2]) + c) * ih[2]));
+    if (MODEL == NS && mu > 0.0) {
+        const double m = a.vl.law == 0 ? mu : visc_mu(a.vl, (double)w[Layout<MODEL>::P] / rho);
+        t = fmax(t, m * kv / rho);
+    }
+    return t >= 0.0 ? t : __longlong_as_double(0x7ff0000000000000ll);  // NaN -> +inf (dt -> 0)
+}
+
+// PACK cells of 16 bytes per component and load where every component starts on a 16-byte
+// boundary (ncell a multiple of PACK), else one.  What bounds it is the memory once the
+// workgroups are few enough: each ends in an atomic on the same word, and 4096 of them took
+// 36 us for a 128^3 FP32 state (42 MB)
+template <typename Real, int MODEL, int PACK>
 __global__ void __launch_bounds__(AUX_THREADS) inv_dt_kernel(const AuxArgs a, const Real* __restrict__ U, double mu,
                                                              unsigned long long* __restrict__ inv_max)
 {
-    constexpr int NC = Layout<MODEL>::NC, V = Layout<MODEL>::V;
+    constexpr int NC = Layout<MODEL>::NC;
     __shared__ double red[AUX_THREADS / 64];
+    struct alignas(sizeof(Real) * PACK) Pack {
+        Real v[PACK];
+    };
     double v = 0.0;
-    const double hmin = fmin(a.dx, fmin(a.dy, a.dz));
-    for (long long q = (long long)blockIdx.x * AUX_THREADS + threadIdx.x; q < a.ncell;
+    const double ih[3] = {1.0 / a.dx, 1.0 / a.dy, 1.0 / a.dz};
+    const double hmin = fmin(a.dx, fmin(a.dy, a.dz)), kv = 14.0 / 3.0 / (hmin * hmin);
+    for (long long q = (long long)blockIdx.x * AUX_THREADS + threadIdx.x; q * PACK < a.ncell;
          q += (long long)gridDim.x * AUX_THREADS) {
-        Real u[NC], w[NC];
+        Pack p[NC];
 #pragma unroll
-        for (int m = 0; m < NC; m++) u[m] = U[m * a.ncell + q];
-        cons_to_prim<Real, MODEL>(mat_of<Real>(a), u, w);
-        const double rho = (double)density<Real, MODEL>(w);
-        const double c = sqrt((double)rhoc2<Real, MODEL>(mat_of<Real>(a), w) / rho);
-        const double s0 = (fabs((double)w[V]) + c) / a.dx;
-        const double s1 = (fabs((double)w[V + 1]) + c) / a.dy;
-        const double s2 = (fabs((double)w[V + 2]) + c) / a.dz;
-        double t = fmax(s0, fmax(s1, s2));
-        if (MODEL == NS && mu > 0.0) {
-            const double m = a.vl.law == 0 ? mu : visc_mu(a.vl, (double)w[Layout<MODEL>::P] / rho);
-            t = fmax(t, m / (3.0 / 14.0 * rho * hmin * hmin));
+        for (int m = 0; m < NC; m++) p[m] = reinterpret_cast<const Pack*>(U + m * a.ncell)[q];
+#pragma unroll
+        for (int k = 0; k < PACK; k++) {
+            Real u[NC];
+#pragma unroll
+            for (int m = 0; m < NC; m++) u[m] = p[m].v[k];
+            v = fmax(v, cell_inverse_dt<Real, MODEL>(a, u, mu, ih, kv));
         }
-        if (!(t >= 0.0)) t = __longlong_as_double(0x7ff0000000000000ll);  // NaN -> +inf (dt -> 0)
-        v = fmax(v, t);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
@@ -275,6 +290,23 @@ __global__ void dt_finish_kernel(unsigned long long* inv_max, double cfl, double
         *dt_out = cfl / m;
         *inv_max = 0ull;
     }
+}
+
+__global__ void batch_fresh_kernel(const BatchScalars* __restrict__ s, const int* __restrict__ count, int before)
+{
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= *count || !s[r].fresh) return;
+    const BatchScalars b = s[r];
+    if (before) *b.t_acc = 0.0;
+    else *b.dt = b.cfl / __longlong_as_double((long long)*b.inv_max);
+    *b.inv_max = 0ull;
+}
+
+hipError_t launch_batch_fresh(const BatchScalars* s, const int* count, int max_n, bool before, hipStream_t st)
+{
+    if (max_n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(batch_fresh_kernel, dim3((max_n + 63) / 64), dim3(64), 0, st, s, count, before ? 1 : 0);
+    return hipGetLastError();
 }
 
 __global__ void batch_dt_finish_kernel(const BatchScalars* __restrict__ s, const int* __restrict__ count)
@@ -313,7 +345,7 @@ hipError_t launch_fill_u8(unsigned char* p, long long n, unsigned char v, hipStr
 
 hipError_t launch_reset_max(unsigned long long* inv_max, hipStream_t st)
 {
-    hipLaunchKernelGGL(reset_u64_kernel, dim3(1), dim3(64), 0, st, inv_max);
+    hipLaunchKernelGGL(reset_max_kernel, dim3(1), dim3(64), 0, st, inv_max);
     return hipGetLastError();
 }
 
@@ -324,38 +356,44 @@ hipError_t launch_dt_finish(unsigned long long* inv_max, double cfl, double* dt_
     return hipGetLastError();
 }
 
-template <typename Real>
-hipError_t launch_dt(const AuxArgs& a, const Real* U, double mu, double cfl, unsigned long long* inv_max,
-                     double* dt_out, double* t_acc, hipStream_t st)
+template <typename Real, int PACK>
+static hipError_t launch_inv_dt_pack(const AuxArgs& a, const Real* U, double mu, unsigned long long* inv_max,
+                                     hipStream_t st)
 {
-    hipLaunchKernelGGL(reset_u64_kernel, dim3(1), dim3(64), 0, st, inv_max);
-    long long nb = (a.ncell + AUX_THREADS - 1) / AUX_THREADS;
-    if (nb > 4096) nb = 4096;
+    long long nb = (a.ncell / PACK + AUX_THREADS - 1) / AUX_THREADS;
+    if (nb > 1024) nb = 1024;
     if (nb < 1) nb = 1;
     switch (a.model) {
-    case EULER: hipLaunchKernelGGL((inv_dt_kernel<Real, EULER>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
-    case NS: hipLaunchKernelGGL((inv_dt_kernel<Real, NS>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
-    default: hipLaunchKernelGGL((inv_dt_kernel<Real, DIM>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
+    case EULER: hipLaunchKernelGGL((inv_dt_kernel<Real, EULER, PACK>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
+    case NS: hipLaunchKernelGGL((inv_dt_kernel<Real, NS, PACK>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
+    default: hipLaunchKernelGGL((inv_dt_kernel<Real, DIM, PACK>), dim3(nb), dim3(AUX_THREADS), 0, st, a, U, mu, inv_max); break;
     }
-    hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(64), 0, st, inv_max, cfl, dt_out, (double*)nullptr,
-                       (const double*)nullptr);
-    if (t_acc) hipLaunchKernelGGL(add_scalar_kernel_fwd, dim3(1), dim3(64), 0, st, t_acc, (const double*)dt_out);
     return hipGetLastError();
 }
-template hipError_t launch_dt<double>(const AuxArgs&, const double*, double, double, unsigned long long*, double*,
-                                      double*, hipStream_t);
-template hipError_t launch_dt<float>(const AuxArgs&, const float*, double, double, unsigned long long*, double*,
-                                     double*, hipStream_t);
 
-__global__ void add_scalar_kernel(double* t_acc, const double* dt)
+template <typename Real>
+hipError_t launch_inv_dt(const AuxArgs& a, const Real* U, double mu, unsigned long long* inv_max, hipStream_t st)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *t_acc += *dt;
+    constexpr int PACK = 16 / sizeof(Real);
+    if (a.ncell % PACK == 0) return launch_inv_dt_pack<Real, PACK>(a, U, mu, inv_max, st);
+    return launch_inv_dt_pack<Real, 1>(a, U, mu, inv_max, st);
 }
-hipError_t launch_add_scalar(double* t_acc, const double* dt, hipStream_t st)
+
+template <typename Real>
+hipError_t launch_dt(const AuxArgs& a, const Real* U, double mu, double cfl, unsigned long long* inv_max,
+                     double* dt_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(add_scalar_kernel, dim3(1), dim3(64), 0, st, t_acc, dt);
-    return hipGetLastError();
+    hipLaunchKernelGGL(reset_max_kernel, dim3(1), dim3(64), 0, st, inv_max);
+    hipError_t e = launch_inv_dt<Real>(a, U, mu, inv_max, st);
+    if (e != hipSuccess) return e;
+    return launch_dt_finish(inv_max, cfl, dt_out, nullptr, nullptr, st);
 }
+template hipError_t launch_inv_dt<double>(const AuxArgs&, const double*, double, unsigned long long*, hipStream_t);
+template hipError_t launch_inv_dt<float>(const AuxArgs&, const float*, double, unsigned long long*, hipStream_t);
+template hipError_t launch_dt<double>(const AuxArgs&, const double*, double, double, unsigned long long*, double*,
+                                      hipStream_t);
+template hipError_t launch_dt<float>(const AuxArgs&, const float*, double, double, unsigned long long*, double*,
+                                     hipStream_t);
 
 // ------------------------------------------------------------------ admissibility scan
 __global__ void reset_check_kernel(long long* w)

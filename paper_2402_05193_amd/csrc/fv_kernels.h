@@ -124,7 +124,11 @@ struct BatchScalars {
     double* dt;                   // time step of the next step
     double* t_acc;                // simulated time
     double cfl;
+    int fresh;                    // its time stepping starts with this membership
 };
+// before and after the first reductions of the fresh members: inv_max = 0, t_acc = 0;
+// dt = cfl / inv_max, inv_max = 0
+hipError_t launch_batch_fresh(const BatchScalars* s, const int* count, int max_n, bool before, hipStream_t st);
 // for every r < *count (device): t_acc += dt; dt = cfl / inv_max; inv_max = 0; the
 // launch covers max_n members
 hipError_t launch_batch_dt_finish(const BatchScalars* s, const int* count, int max_n, hipStream_t st);
@@ -147,22 +151,24 @@ template <typename Real>
 hipError_t launch_init(const AuxArgs& a, int case_id, const double* params, int nparams, uint64_t seed, Real* U,
                        hipStream_t st);
 // max over cells of the inverse CFL time step into *inv_max (uint64 bit pattern of a
-// non-negative double); then dt = cfl / max and *t_acc += dt (if t_acc).
+// non-negative double); then dt = cfl / max; *inv_max is left at zero.
 template <typename Real>
 hipError_t launch_dt(const AuxArgs& a, const Real* U, double mu, double cfl, unsigned long long* inv_max,
-                     double* dt_out, double* t_acc, hipStream_t st);
+                     double* dt_out, hipStream_t st);
+// the reduction alone: atomic maximum into *inv_max
+template <typename Real>
+hipError_t launch_inv_dt(const AuxArgs& a, const Real* U, double mu, unsigned long long* inv_max, hipStream_t st);
 // admissibility / finiteness scan; ws_words: [0] first bad index (int64, init INT64_MAX),
 // [1] count, [2] worst code
 template <typename Real>
 hipError_t launch_check(const AuxArgs& a, const Real* U, long long* ws_words, hipStream_t st);
-hipError_t launch_add_scalar(double* t_acc, const double* dt, hipStream_t st);
 // *inv_max = 0
 hipError_t launch_reset_max(unsigned long long* inv_max, hipStream_t st);
-// p[0 .. n) = v (a kernel, so that it can be captured in a graph)
-hipError_t launch_fill_u8(unsigned char* p, long long n, unsigned char v, hipStream_t st);
 // t_acc (optional) += *dt_prev;  *dt_out = cfl / max;  *inv_max = 0
 hipError_t launch_dt_finish(unsigned long long* inv_max, double cfl, double* dt_out, double* t_acc,
                             const double* dt_prev, hipStream_t st);
+// p[0 .. n) = v (a kernel, so that it can be captured in a graph)
+hipError_t launch_fill_u8(unsigned char* p, long long n, unsigned char v, hipStream_t st);
 
 // Discrete adjoint of the single-phase Euler right-hand side (fv_adjoint.hip).
 struct AdjointArgs {
