@@ -182,29 +182,34 @@ bool positivity_on(const fv_config* c)
 
 // Planes per z chunk of a single-problem launch of `tiles` tile columns: the chunk with the
 // least estimated time, (planes + start) x the time per plane of a CU's fullest load.  A
-// chunk's start (window loads, z-only and warm-up steps) costs about one plane step
-// (FP32 half of one), and with n workgroups on a CU, of which S run at once (2 FP64, 3
-// FP32), a plane step of each takes f(n) times that of one alone, f(2) = 1.38 in FP64,
-// f(2) = 1.2 and f(3) = 1.6 in FP32, and full rounds of S follow each other.  The constants
-// are fitted to stage times at 120 sizes from 200x1x1 to 256^3 of the three models, each
-// with chunks of 1 to 128 planes: the estimate's choice is within 0.1 % of the fastest
-// chunk on average in FP64 and within 1 % in FP32 (longest chunks 128 and 16 planes:
-// FP32 256^3 measured 2-3 % slower with 32).  Against the rule that batched members keep, ms
-// per stage: Euler 32^3 0.037 -> 0.016, 64^3 0.041 -> 0.033, 128^3 0.191 -> 0.172; NS 176^3
-// 0.721 -> 0.658, 256^3 1.874 -> 1.832; five-equation 200^3 1.88 -> 1.56, 256^3 2.74 -> 2.60,
-// FP32 192x96x96 0.226 -> 0.169.  Results do not depend on the chunks.
-int solo_zchunk(long long tiles, int nz, bool f64)
+// chunk's start (window loads, z-only and warm-up steps) costs about one plane step, and
+// with n workgroups on a CU, of which S run at once, a plane step of each takes load[n]
+// times that of one alone; full rounds of S follow each other.  S: 2 in FP64, 3 in FP32, 4
+// for the FP32 single-phase primitive WENO5-Z kernels without limiters (116 VGPRs).  The
+// constants are fitted to stage times at 150 sizes from 200x1x1 to 256^3 of the three
+// models, each with chunks of 1 to 128 planes: the estimate's choice is within 0.1 % of the
+// fastest chunk on average in FP64, within 0.3 % and 2 % in FP32.  Against the rule that
+// batched members keep, ms per stage: Euler 32^3 0.037 -> 0.016, 64^3 0.041 -> 0.033, 128^3
+// 0.191 -> 0.172; NS 176^3 0.721 -> 0.658, 256^3 1.874 -> 1.832, FP32 128^3 0.186 -> 0.149;
+// five-equation 200^3 1.88 -> 1.56, 256^3 2.74 -> 2.60, FP32 192x96x96 0.226 -> 0.169.
+// Results do not depend on the chunks.
+int solo_zchunk(const fv_config* c, long long tiles)
 {
-    const int S = f64 ? 2 : 3, longest = f64 ? 128 : 16;
-    const double start = f64 ? 1.0 : 0.5;
-    const double load64[3] = {0.0, 1.0, 1.38}, load32[4] = {0.0, 1.0, 1.2, 1.6};
-    const double* load = f64 ? load64 : load32;
+    struct Fit {
+        int S, longest;
+        double start, load[5];
+    };
+    static const Fit f64 = {2, 128, 1.0, {0.0, 1.0, 1.38}};
+    static const Fit f32 = {3, 8, 0.5, {0.0, 1.0, 1.3, 1.6}};
+    static const Fit f32_four = {4, 11, 1.0, {0.0, 1.0, 1.1, 1.35, 1.8}};
+    const bool four = c->model != FV_DIM && !positivity_on(c) && !c->recon && !c->scheme;
+    const Fit& f = c->dtype == FV_F64 ? f64 : (four ? f32_four : f32);
     int best = 1;
     double best_t = 0.0;
-    for (int z = 1; z <= longest && z <= nz; z++) {
-        const int chunks = (nz + z - 1) / z;
+    for (int z = 1; z <= f.longest && z <= c->nz; z++) {
+        const int chunks = (c->nz + z - 1) / z;
         const long long n = (tiles * chunks + RESIDENT_CUS - 1) / RESIDENT_CUS;
-        const double t = (z + start) * ((double)(n / S) * load[S] + load[n % S]);
+        const double t = (z + f.start) * ((double)(n / f.S) * f.load[f.S] + f.load[n % f.S]);
         if (z == 1 || t <= best_t) {
             best = z;
             best_t = t;
@@ -233,7 +238,7 @@ fv::StageArgs<Real> stage_args(const fv_config* c, fv::LaunchGeom& g, bool solo 
     if (nch < 1) nch = 1;
     int zc = (c->nz + nch - 1) / nch;
     if (solo) {
-        zc = solo_zchunk(tiles, c->nz, f64);
+        zc = solo_zchunk(c, tiles);
     } else if (zc < FV_MIN_ZCHUNK) {
         zc = FV_MIN_ZCHUNK < c->nz ? FV_MIN_ZCHUNK : c->nz;
         const long long slots = (long long)RESIDENT_CUS * (f64 ? 2 : 3);
