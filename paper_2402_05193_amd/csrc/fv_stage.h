@@ -394,14 +394,16 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         // phases (five-equation FP64: VGPR spills 106 -> 93, and its loads no longer wait at
         // the end of the previous step to be spilled: 0.914 -> 0.888 ms per stage at
         // 256x128x128, THINC 1.357 -> 1.316, FP32 1-2 % faster; Euler 256^3 1.673 -> 1.649
-        // ms, FP32 0.953 -> 0.934, characteristic 2.274 -> 2.246).  The five-equation FP64
+        // ms, FP32 0.953 -> 0.934, characteristic 2.274 -> 2.246; NS FP64 with external viscous
+        // fluxes, TENO6-A step at 128^3 2.18 -> 2.12).  The five-equation FP64
         // TENO6-A and characteristic kernels and the Euler TENO6-A kernels measured 0.2-2 %
         // slower so and keep an early load.  An early load is issued after the step's other
         // loads for the remaining FP64 single-phase kernels (LATE_OWN: its conversion waits
         // for it and would hold them back), else at the start of the step (measured faster
         // so); either way it is converted once those loads are issued.
         constexpr bool OWN_AFTER_Z =
-            (MODEL == DIM && (sizeof(Real) == 4 || REC == REC_WENO_PRIM)) || (MODEL == EULER && !TENO);
+            (MODEL == DIM && (sizeof(Real) == 4 || REC == REC_WENO_PRIM)) || (MODEL == EULER && !TENO) ||
+            (MODEL == NS && !VISC && sizeof(Real) == 8 && !CHARV);
         constexpr bool LATE_OWN = MODEL != DIM && sizeof(Real) == 8 && !OWN_AFTER_Z;
         Real raw[NC];
         int rrefl = 0;
