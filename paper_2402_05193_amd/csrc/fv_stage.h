@@ -288,7 +288,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     // would not be a number keeps that in its result (one_cell_axis).  y: the rows of the
     // tile beyond the only one are left out of the x phases too.  z: one plane step and the
     // finalisation.  What bounds these launches is the latency of one workgroup's march:
-    // per stage a tube of 200 cells 24 -> 10 us (five-equation FP64), 150x150x1 16 -> 13 us
+    // per stage a tube of 200 cells 24 -> 11 us (five-equation FP64), 150x150x1 16 -> 13 us
     // (Euler FP64).  A kernel of its own: as a run-time switch it made the large grids 3-4 %
     // slower.
     static_assert(!(FLAT && REC_FLAGS), "the kernel that records limiter decisions does every face");
