@@ -196,7 +196,8 @@ struct Tile {
 
 // One workgroup of the fused stage: tile column `bid` of the problem described by `a`.
 // FLAT: for grids of one cell along y or z (see one_cell_axis).
-template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH, bool FLAT = false>
+// SPREAD: the whole launch is this problem; its workgroups are reordered over the XCDs.
+template <typename Real, int MODEL, int POS, int REC, int VMODE, int BX, int BY, int NTH, bool FLAT = false, bool SPREAD = false>
 __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int bid, unsigned char* smem_raw)
 {
     using L = Layout<MODEL>;
@@ -238,10 +239,23 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     const int tid = threadIdx.x;
     const bool has_cell = tid < NCELL;  // threads beyond the tile only take x/y tasks
     const int tx = tid % BX, ty = has_cell ? tid / BX : 0;
-    int b = bid;
-    // blocks of one tile column are consecutive; consecutive tiles share an XCD's L2
-    const int chunk = b % a.nchunks;
-    b /= a.nchunks;
+    int b = bid, chunk;
+    if constexpr (SPREAD) {
+        // Consecutive workgroups go to the eight XCDs in turn; each XCD takes a contiguous
+        // range of the tiles of a z chunk, so that most halo columns are in its own L2 (with
+        // a tile's chunks next to each other and few of them, neighbouring tiles were on
+        // different XCDs and every one fetched its halo itself).  us per stage: NS 256^3 1843
+        // -> 1825, 205x171x94 455 -> 436, FP32 65x68x81 71 -> 65, Euler 32^3 16 -> 15; the
+        // five-equation 256x128x128 623 -> 620.
+        const int n = (int)gridDim.x, x = b & 7, tiles = a.tiles_x * a.tiles_y;
+        b = x * (n >> 3) + min(x, n & 7) + (b >> 3);
+        chunk = b / tiles;
+        b -= chunk * tiles;
+    } else {
+        // blocks of one tile column are consecutive
+        chunk = b % a.nchunks;
+        b /= a.nchunks;
+    }
     const int tileX = b % a.tiles_x;
     const int tileY = b / a.tiles_x;
     const int x0 = tileX * BX, y0 = tileY * BY;
@@ -1217,7 +1231,7 @@ __global__ void __launch_bounds__(NTH, stage_waves<Real>()) stage_kernel(const S
     // the argument block read in place from the kernel-argument segment (fewer scalar
     // registers than a copy)
     const StageArgs<Real>* pa = (const StageArgs<Real>*)__builtin_amdgcn_kernarg_segment_ptr();
-    stage_body<Real, MODEL, POS, REC, VMODE, BX, BY, NTH>(*pa, (int)blockIdx.x, smem_raw);
+    stage_body<Real, MODEL, POS, REC, VMODE, BX, BY, NTH, false, true>(*pa, (int)blockIdx.x, smem_raw);
 }
 
 // The same for grids of one cell along y or z
