@@ -23,6 +23,7 @@
 //    (combined with U^n and written once, coalesced, x fastest).
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 
 #include "fv_kernels.h"
@@ -307,8 +308,26 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     // slower.
     static_assert(!(FLAT && REC_FLAGS), "the kernel that records limiter decisions does every face");
     const bool one_y = FLAT && a.ny == 1, one_z = FLAT && a.nz == 1;
-    auto one_cell_axis = [&](const Real* w) {
-        return density<Real, MODEL>(w) > Real(0) && rhoc2<Real, MODEL>(mat, w) > Real(0) ? Real(0) : Real(NAN);
+    // d: the difference of a cell's two face fluxes along such an axis (0 y, 1 z).  Zero, or not
+    // a number where the flux is none: no speed of sound, or its square beyond the type's
+    // range; the momenta and the energy where the law has no viscosity at the cell's
+    // temperature; the energy where its flux, the largest term, is beyond the range.
+    auto one_cell_axis = [&](const Real* w, int axis, Real* d) {
+        constexpr Real most = sizeof(Real) == 8 ? Real(DBL_MAX) : Real(FLT_MAX);
+        const Real rho = density<Real, MODEL>(w), rc2 = rhoc2<Real, MODEL>(mat, w);
+        const Real d0 = rc2 > Real(0) && rc2 < most * rho ? Real(0) : Real(NAN);
+#pragma unroll
+        for (int m = 0; m < NC; m++) d[m] = d0;
+        if constexpr (VLAW) {
+            if (!(w[P] > Real(0))) {
+                const Real muc = visc_mu(a.vl, w[P] * rcp(rho));
+#pragma unroll
+                for (int m = V; m <= P; m++) d[m] += muc - muc;
+            }
+        }
+        const Real ke = Real(0.5) * rho * (w[V] * w[V] + w[V + 1] * w[V + 1] + w[V + 2] * w[V + 2]);
+        const Real fe = w[V + 1 + axis] * (rho_e<Real, MODEL>(mat, w) + ke + w[P]);
+        d[P] += fe - fe;
     };
     // viscous: two warm-up planes for the in-plane derivatives of the first z faces;
     // THINC: one, for the in-plane volume-fraction gradient of cell z0-1
@@ -720,9 +739,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 Real wl[NC], wr[NC], F[NC], uh;
                 if (one_z) {
                     uh = Real(0);
-                    F[0] = one_cell_axis(win[1 + WO]);
-#pragma unroll
-                    for (int m = 1; m < NC; m++) F[m] = F[0];
+                    one_cell_axis(win[1 + WO], 1, F);
                 } else {
                 if constexpr (VISC) {
                     // viscous part first: its inputs are the window and the carried derivatives
@@ -1005,11 +1022,12 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 }
                 if constexpr (MODEL == DIM) srcC = (UHB[fl + 1] - UHB[fl]) * idx;
                 if (one_y) {
-                    const Real d = one_cell_axis(win[3 + WO]);
+                    Real d[NC];
+                    one_cell_axis(win[3 + WO], 0, d);
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
-                        if constexpr (ACC_LDS) slot[m * NCELL] -= d;
-                        else accC[m] -= d;
+                        if constexpr (ACC_LDS) slot[m * NCELL] -= d[m];
+                        else accC[m] -= d[m];
                     }
                 }
             }

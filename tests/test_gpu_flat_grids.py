@@ -77,3 +77,45 @@ def test_flat_inadmissible_cell_gives_nan(shape):
     U[4, 0, 0, 4] = -1.0
     R = S.rhs(cfg, U, torch.empty_like(U))
     assert torch.isnan(R[:, 0, 0, 4]).all()
+
+
+@pytest.mark.parametrize("shape", [(9, 1, 1), (9, 8, 1), (9, 1, 6)])
+@pytest.mark.parametrize("law", [1, 2])
+def test_flat_viscosity_law_below_zero_temperature(shape, law):
+    """A cell in tension (p < 0 < p + p_inf) has a convective flux but no viscosity at its
+    temperature p / rho: not a number where the recording kernel has none, else equal."""
+    cfg = config(shape, S.NS, S.F64, PERIODIC, 1)
+    cfg.pinf1, cfg.visc_law, cfg.T_ref, cfg.sutherland = 10.0, law, 0.9, 0.35
+    U = state(cfg, 8)
+    W = S.cons_to_prim(cfg, U, torch.empty_like(U))
+    W[4, 0, 0, 4] = -0.5
+    U = S.prim_to_cons(cfg, W, U)
+    R, _ = S.rhs_flags(cfg, U, torch.empty_like(U), 1e-3)
+    got = S.rhs(cfg, U, torch.empty_like(U), 1e-3)
+    assert torch.isnan(R[1:, 0, 0, 4]).all() and torch.isfinite(R[:, 0, 0, 0]).all()
+    assert torch.equal(got.nan_to_num(nan=1e30), R.nan_to_num(nan=1e30))
+
+
+@pytest.mark.parametrize("model", [S.EULER, S.DIM])
+@pytest.mark.parametrize("axis", [1, 2])
+@pytest.mark.parametrize("scale", [1.0, 1e13])
+def test_flat_flux_beyond_the_range(model, axis, scale):
+    """Uniform flow along an axis of one cell: finite, or (FP32, energy flux of 1e41) not a
+    number, as the recording kernel has it."""
+    cfg = config((9, 1, 1), model, S.F32, PERIODIC, 1)
+    v = 2 if model == S.DIM else 1
+    W = torch.ones(cfg.shape, device="cuda")
+    W[:v] = 1.0 / v
+    W[v:v + 3] = 0.0
+    W[v + axis] = scale
+    W[v + 3] = scale * scale * 100.0
+    if model == S.DIM:
+        W[6] = 0.5
+    U = S.prim_to_cons(cfg, W, S.empty_state(cfg))
+    assert torch.isfinite(U).all()
+    R, _ = S.rhs_flags(cfg, U, torch.empty_like(U), 1e-20)
+    got = S.rhs(cfg, U, torch.empty_like(U), 1e-20)
+    assert torch.isfinite(R[v + 3]).all() == (scale == 1.0)
+    assert torch.equal(torch.isnan(got), torch.isnan(R))
+    if scale == 1.0:
+        assert torch.equal(got, R)
