@@ -12,6 +12,7 @@
 
 #include "../../include/fvrk3.h"
 #include "fv_kernels.h"
+#include "fv_launch_plan.h"
 
 namespace {
 
@@ -204,13 +205,17 @@ int solo_zchunk(const fv_config* c, long long tiles)
     static const Fit f32_four = {4, 11, 1.0, {0.0, 1.0, 1.1, 1.35, 1.8}};
     const bool four = c->model != FV_DIM && !positivity_on(c) && !c->recon && !c->scheme;
     const Fit& f = c->dtype == FV_F64 ? f64 : (four ? f32_four : f32);
-    int best = 1;
+    // lines and sheets of many planes leave most of a tile empty: no launch holds their
+    // workgroups at the longest chunk of the fit (FP32 1x1xn beyond n = 1.3e8)
+    const int shortest = fv::shortest_zchunk(tiles, c->nz, TILE_NT);
+    const int longest = f.longest > shortest ? f.longest : shortest;
+    int best = shortest;
     double best_t = 0.0;
-    for (int z = 1; z <= f.longest && z <= c->nz; z++) {
+    for (int z = shortest; z <= longest && z <= c->nz; z++) {
         const int chunks = (c->nz + z - 1) / z;
         const long long n = (tiles * chunks + RESIDENT_CUS - 1) / RESIDENT_CUS;
         const double t = (z + f.start) * ((double)(n / f.S) * f.load[f.S] + f.load[n % f.S]);
-        if (z == 1 || t <= best_t) {
+        if (z == shortest || t <= best_t) {
             best = z;
             best_t = t;
         }

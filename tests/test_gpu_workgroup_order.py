@@ -37,3 +37,20 @@ def test_every_cell_is_reached(shape, model, dtype):
     for (_, U, _), V in zip(members, alone):
         assert torch.equal(U, V)
     b.close()
+
+
+def test_long_line():
+    """A line of so many cells along z that chunks of the usual length would exceed the
+    threads of one launch: periodic data, every period bit for bit that of a short line."""
+    n, periods = 100, 1343000
+    kw = dict(nx=1, ny=1, dx=0.1, dy=0.1, dz=0.1, model=S.EULER, dtype=S.F32)
+    small, large = S.Config(nz=n, **kw), S.Config(nz=n * periods, **kw)
+    z = torch.arange(n, device="cuda", dtype=torch.float32) * (2 * np.pi / n)
+    W = torch.ones(small.shape, device="cuda")
+    W[0, :, 0, 0] += 0.2 * torch.sin(z)
+    W[3, :, 0, 0] = 0.3 * torch.cos(z)
+    U = S.prim_to_cons(small, W, S.empty_state(small))
+    R = S.rhs(small, U, torch.empty_like(U))
+    U = U.repeat(1, periods, 1, 1)
+    got = S.rhs(large, U, torch.full_like(U, float("nan")))
+    assert torch.equal(got.view(5, periods, n), R.view(5, 1, n).expand(5, periods, n))
