@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fv_kernels.h"
+#include "fv_launch_plan.h"
 
 namespace fv {
 
@@ -279,7 +280,8 @@ __device__ __forceinline__ void hllc_vjp(const Material<double>& mat, const doub
 //            collected across the threads through LDS;
 //   cell p   the cotangents of halo positions added to the cells they mirror, the reverse
 //            sweep of U -> W, and the sum into Ubar.
-// A periodic line that fits a workgroup closes on itself (positions 0 .. n-1, no halo).
+// A periodic line that fits a workgroup, and any line of one cell, closes on itself
+// (positions 0 .. n-1, no halo).
 // What bounds it: the latency of that chain (~1700 vector instructions) at three waves per
 // SIMD.  A thread per face, which rebuilt ten cell reconstructions and added 30 values with
 // atomics at one wave per SIMD, took 214 us per right-hand side at 64^3; this takes 69
@@ -288,27 +290,6 @@ __device__ __forceinline__ void hllc_vjp(const Material<double>& mat, const doub
 // 1.51, 128 threads at three 2.75 / 1.47.  One launch for the three directions, meeting in
 // five atomic additions per cell and direction, against three launches that add without
 // atomics: 2.45 against 2.62 ms, at 24^3 1.51 against 1.98, at 128^3 equal within 1 %.
-constexpr int ADJ_NT = 256;    // threads of a workgroup
-constexpr int ADJ_CELLS = 64;  // longest piece of a line in one workgroup
-
-// pieces of a line: all of it when periodic and short, else equal pieces of at most
-// ADJ_CELLS cells (of 32 or more when there are several, so that a boundary's three halo
-// positions and their mirror images lie in one piece); slots = positions per line
-struct AdjointSplit {
-    int pieces, slots, lines;  // per line; per piece; lines of a workgroup
-    bool closed;               // the line closes on itself
-};
-
-__host__ __device__ inline AdjointSplit adjoint_split(int n, bool periodic)
-{
-    AdjointSplit s;
-    s.closed = periodic && n <= ADJ_CELLS + 7;
-    s.pieces = s.closed ? 1 : (n + ADJ_CELLS - 1) / ADJ_CELLS;
-    s.slots = s.closed ? n : (n + s.pieces - 1) / s.pieces + 7;
-    s.lines = ADJ_NT / s.slots;
-    return s;
-}
-
 struct AdjointLds {
     // primitive states of the slots and, in pieces of a line, of two more positions on
     // either side (4 lines <= ADJ_NT / 2 entries: a piece has at least 8 slots)
@@ -329,7 +310,7 @@ __device__ __forceinline__ void rhs_adjoint_body(AdjointLds& lds, const AdjointA
     auto& X = lds.X;
     const int n = DIR == 0 ? a.nx : (DIR == 1 ? a.ny : a.nz);
     const int SL = sp.slots, LN = sp.lines;
-    const bool periodic = a.bc[2 * DIR] == PERIODIC;
+    const bool periodic = sp.closed || a.bc[2 * DIR] == PERIODIC;
     const int tid = threadIdx.x;
     // (slot, line): along x the slots are consecutive in memory, else the lines are
     const int slot = DIR == 0 ? tid % SL : tid / LN, ln = DIR == 0 ? tid / SL : tid % LN;
@@ -540,16 +521,17 @@ __device__ __forceinline__ void rhs_adjoint_body(AdjointLds& lds, const AdjointA
     }
 }
 
-// the three directions in one launch: blocks [0, b1) take x, [b1, b2) y, the rest z
+// the three directions in one launch: blocks [0, b1) take x, [b1, b2) y, the rest z; the
+// launch covers the blocks from `base` on
 __global__ void __launch_bounds__(ADJ_NT, 3) rhs_adjoint_all(const AdjointArgs a, const AdjointSplit sx,
                                                             const AdjointSplit sy, const AdjointSplit sz,
-                                                            const unsigned b1, const unsigned b2,
+                                                            const unsigned b1, const unsigned b2, const unsigned base,
                                                             const double* __restrict__ U,
                                                             const double* __restrict__ Rbar,
                                                             double* __restrict__ Ubar, const double scale)
 {
     __shared__ AdjointLds lds;
-    const unsigned b = blockIdx.x;
+    const unsigned b = base + blockIdx.x;
     if (b < b1) rhs_adjoint_body<0>(lds, a, sx, b, U, Rbar, Ubar, scale);
     else if (b < b2) rhs_adjoint_body<1>(lds, a, sy, b - b1, U, Rbar, Ubar, scale);
     else rhs_adjoint_body<2>(lds, a, sz, b - b2, U, Rbar, Ubar, scale);
@@ -580,15 +562,24 @@ hipError_t launch_rhs_adjoint(const AdjointArgs& a, const double* U, const doubl
 {
     const int n3[3] = {a.nx, a.ny, a.nz};
     AdjointSplit sp[3];
-    unsigned blocks[3], total = 0;
+    long long end[3], total = 0;
     for (int d = 0; d < 3; d++) {
         sp[d] = adjoint_split(n3[d], a.bc[2 * d] == PERIODIC);
-        blocks[d] = (unsigned)((a.ncell / n3[d] + sp[d].lines - 1) / sp[d].lines * sp[d].pieces);
-        total += blocks[d];
+        end[d] = total += adjoint_blocks(sp[d], a.ncell / n3[d]);
     }
-    hipLaunchKernelGGL(rhs_adjoint_all, dim3(total), dim3(ADJ_NT), 0, st, a, sp[0], sp[1], sp[2], blocks[0],
-                       blocks[0] + blocks[1], U, Rbar, Ubar, scale);
-    return hipGetLastError();
+    // the kernel's 32-bit line and block numbers: more would not fit the memory
+    if (total > 0xffffffffll || a.ncell / n3[0] > 0xffffffffll || a.ncell / n3[1] > 0xffffffffll ||
+        a.ncell / n3[2] > 0xffffffffll)
+        return hipErrorInvalidValue;
+    // one launch, but for the largest grids (1024^3: 3 x 5592416 workgroups)
+    for (long long base = 0; base < total; base += max_blocks(ADJ_NT)) {
+        const long long nb = total - base < max_blocks(ADJ_NT) ? total - base : max_blocks(ADJ_NT);
+        hipLaunchKernelGGL(rhs_adjoint_all, dim3((unsigned)nb), dim3(ADJ_NT), 0, st, a, sp[0], sp[1], sp[2],
+                           (unsigned)end[0], (unsigned)end[1], (unsigned)base, U, Rbar, Ubar, scale);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_lincomb(double* out, long long n, double c0, const double* x0, double c1, const double* x1, double c2,
