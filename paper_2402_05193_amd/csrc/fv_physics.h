@@ -512,7 +512,8 @@ __device__ __forceinline__ void teno6a_pair(Real a, Real b, Real c, Real d, Real
 // velocities and the volume fraction unchanged; each is reconstructed from both
 // sides and mapped back with K.  (WENO5-Z does not see a per-field scale;
 // TENO6-A's cut-off does, so the variables are K^{-1} W exactly.)
-template <typename Real, int MODEL, int DIR, bool TENO, typename Stencil>
+// ORDERED: one field after the other (the stage kernel's CHAR_ORDERED).
+template <typename Real, int MODEL, int DIR, bool TENO, bool ORDERED, typename Stencil>
 __device__ __forceinline__ void char_face_states(const Material<Real>& mat, Stencil st, Real eps, Real* wl, Real* wr)
 {
     constexpr int NC = Layout<MODEL>::NC, V = Layout<MODEL>::V, P = Layout<MODEL>::P;
@@ -538,11 +539,7 @@ __device__ __forceinline__ void char_face_states(const Material<Real>& mat, Sten
         } else {
             weno5z_face(q, eps, L, R);
         }
-        // one field after the other (five-equation FP64 WENO5-Z 80 -> 12 spilled VGPRs,
-        // 706 -> 614 us per step at 160x80x80; TENO6-A with THINC 325 -> 113, 2207 ->
-        // 1571 us).  Without spills to avoid, the single-phase FP64 WENO5-Z kernels lost
-        // 2 % with it.
-        if constexpr (MODEL == DIM || TENO || sizeof(Real) == 4) {
+        if constexpr (ORDERED) {
             pin(L);
             pin(R);
         }

@@ -293,6 +293,14 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     constexpr bool FACE = REC != REC_WENO_PRIM;
     constexpr bool CHARV = REC == REC_WENO_CHAR || REC == REC_TENO_CHAR;
     constexpr bool TENO = REC == REC_TENO_PRIM || REC == REC_TENO_CHAR;
+    // characteristic fields one after the other (char_face_states) where interleaved ones
+    // spill: five-equation FP64 WENO5-Z 80 -> 12 spilled VGPRs, 706 -> 614 us per step at
+    // 160x80x80; TENO6-A with THINC 325 -> 113, 2207 -> 1571 us.  Without spills to avoid, the
+    // single-phase FP64 WENO5-Z kernels lost 2 % with it; with a viscosity law and limiters
+    // they spill 57 VGPRs, all but 2 of them for the z faces: in order there, NS 128^3 1361 ->
+    // 1197 us per step, 200x1x1 139 -> 120 (in order on every axis 1224, 122).
+    constexpr bool CHAR_ORDERED = MODEL == DIM || TENO || sizeof(Real) == 4;
+    constexpr bool CHAR_ORDERED_Z = CHAR_ORDERED || (VLAW && POS);
     // register window W(s-3 .. s+2) of the own column
     constexpr int NWIN = FACE ? 7 : 6, WO = FACE ? 1 : 0;  // face tasks need s-4 .. s+2
     Real win[NWIN][NC];
@@ -768,7 +776,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 }
                 if constexpr (CHARV) {
                     // characteristic variables of the face's frozen state, stencil s-4 .. s+1
-                    char_face_states<Real, MODEL, 2, TENO>(mat, [&](int q, int m) { return win[q][m]; }, weps, wl, wr);
+                    char_face_states<Real, MODEL, 2, TENO, CHAR_ORDERED_Z>(mat, [&](int q, int m) { return win[q][m]; }, weps, wl, wr);
                 } else if constexpr (TENO) {
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
@@ -893,7 +901,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 for (int t = rt; t < TL::NFX; t += NT) {
                     const int j = t / (BX + 1), f = t - j * (BX + 1);
                     Real wl[NC], wr[NC];
-                    char_face_states<Real, MODEL, 0, TENO>(mat, [&](int q, int m) { return wp(m, f - 3 + q, j); }, weps,
+                    char_face_states<Real, MODEL, 0, TENO, CHAR_ORDERED>(mat, [&](int q, int m) { return wp(m, f - 3 + q, j); }, weps,
                                                            wl, wr);
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
@@ -1041,7 +1049,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 for (int t = rt; t < TL::NFY; t += NT) {
                     const int f = t / BX, i = t - f * BX;
                     Real wl[NC], wr[NC];
-                    char_face_states<Real, MODEL, 1, TENO>(mat, [&](int q, int m) { return wp(m, i, f - 3 + q); }, weps,
+                    char_face_states<Real, MODEL, 1, TENO, CHAR_ORDERED>(mat, [&](int q, int m) { return wp(m, i, f - 3 + q); }, weps,
                                                            wl, wr);
 #pragma unroll
                     for (int m = 0; m < NC; m++) {
