@@ -153,6 +153,7 @@ struct Tile {
     static constexpr int NC = Layout<MODEL>::NC;
     static constexpr bool VISC = VISC_;  // the stage computes viscous fluxes itself
     static constexpr bool THINC = THINC_;  // interface capturing (five-equation model)
+    static_assert(BX % 2 == 0 && BY % 2 == 0, "the x and y reconstructions take two cells at a time");
     static constexpr int NT = NTH;
     static constexpr int NCELL = BX * BY;
     static constexpr int PX = BX + 6, PY = BY + 6;  // plane with 3-cell halo
@@ -420,7 +421,7 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
         // FP32 16 -> 0 (168 -> 139 VGPRs), five-equation FP64 84 -> 70; per stage NS 256^3
         // 2.40 -> 2.06 ms, five-equation THINC FP32 192x96x96 0.33 -> 0.30
         int tid = threadIdx.x;
-                pin(tid);
+        pin(tid);
         const bool has_cell = tid < NCELL;
         const int tx = tid % BX, ty = has_cell ? tid / BX : 0;
         // task lists have a few tasks more than threads; the wave that takes the
