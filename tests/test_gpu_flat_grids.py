@@ -119,3 +119,52 @@ def test_flat_flux_beyond_the_range(model, axis, scale):
     assert torch.equal(torch.isnan(got), torch.isnan(R))
     if scale == 1.0:
         assert torch.equal(got, R)
+
+
+def walls(shape):
+    """Symmetry planes on the axes that can hold them, open boundaries on the others."""
+    return tuple(b for n in shape for b in ((S.SYMMETRY, S.ZERO_GRADIENT) if n >= 3 else OPEN[:2]))
+
+
+VARIANTS = [dict(model=S.EULER), dict(model=S.NS, visc_law=1, T_ref=0.9), dict(model=S.NS, visc_law=2, sutherland=0.35),
+            dict(model=S.DIM), dict(model=S.DIM, thinc=1)]
+
+
+def variant(shape, dtype, bc, positivity, kw):
+    cfg = config(shape, kw["model"], dtype, bc, positivity)
+    for k, v in kw.items():
+        setattr(cfg, k, v)
+    return cfg
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("kw", VARIANTS)
+@pytest.mark.parametrize("dtype", [S.F64, S.F32])
+def test_flat_rhs_with_walls_and_viscosity_laws(shape, kw, dtype):
+    cfg = variant(shape, dtype, walls(shape), 1, kw)
+    U = state(cfg, 4)
+    R, _ = S.rhs_flags(cfg, U, torch.empty_like(U), 1e-3)
+    got = S.rhs(cfg, U, torch.full_like(U, float("nan")), 1e-3)
+    assert torch.isfinite(got).all()
+    assert torch.equal(got, R)
+
+
+@pytest.mark.parametrize("shape", SHAPES[:5])
+@pytest.mark.parametrize("kw", VARIANTS)
+def test_flat_advance_with_walls_and_viscosity_laws(shape, kw):
+    """The stages with their CFL reduction, against the batched kernel."""
+    members, alone = [], []
+    for k in range(2):
+        cfg = variant(shape, S.F64, walls(shape) if k else PERIODIC, 1, kw)
+        U, ws = state(cfg, 20 + k), S.workspace(cfg)
+        V = U.clone()
+        alone.append((V, S.advance(cfg, V, 3, 0.0, ws, t=0.0)))
+        members.append((cfg, U, S.workspace(cfg)))
+    b = S.Batch(2)
+    b.set(members, fresh=[1, 1])
+    b.step(3)
+    torch.cuda.synchronize()
+    for (cfg, U, ws), (V, t) in zip(members, alone):
+        assert torch.isfinite(U).all() and torch.equal(U, V)
+        assert S.workspace_time(cfg, ws) == t
+    b.close()

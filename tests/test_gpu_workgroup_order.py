@@ -54,3 +54,31 @@ def test_long_line():
     U = U.repeat(1, periods, 1, 1)
     got = S.rhs(large, U, torch.full_like(U, float("nan")))
     assert torch.equal(got.view(5, periods, n), R.view(5, 1, n).expand(5, periods, n))
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 9), (33, 17, 3), (50, 35, 7)])
+@pytest.mark.parametrize("kw", [dict(model=S.DIM, thinc=1), dict(model=S.DIM, recon=1, dtype=S.F32),
+                                dict(model=S.EULER, recon=1), dict(model=S.EULER, scheme=1, dtype=S.F32),
+                                dict(model=S.NS, recon=1, scheme=1), dict(model=S.NS, visc_law=2, sutherland=0.4)])
+def test_every_cell_is_reached_by_the_other_variants(shape, kw):
+    members, alone = [], []
+    for k in range(2):
+        cfg = S.Config(nx=shape[0], ny=shape[1], nz=shape[2], dx=0.1, dy=0.12, dz=0.09, mu=1e-2, gamma2=1.66,
+                       bc=(S.PERIODIC,) * 6 if k else (S.ZERO_GRADIENT,) * 6, **kw)
+        rng = np.random.default_rng(11 + k)
+        W = 1.0 + 0.1 * rng.random(cfg.shape)
+        if cfg.model == S.DIM:
+            W[6] = 0.2 + 0.6 * rng.random(W[6].shape)
+        U = S.prim_to_cons(cfg, torch.from_numpy(W).to("cuda", cfg.torch_dtype).contiguous(), S.empty_state(cfg))
+        V = U.clone()
+        S.advance(cfg, V, 2, 0.0, S.workspace(cfg))
+        assert torch.isfinite(V).all()
+        alone.append(V)
+        members.append((cfg, U, S.workspace(cfg)))
+    b = S.Batch(2)
+    b.set(members, fresh=[1, 1])
+    b.step(2)
+    torch.cuda.synchronize()
+    for (_, U, _), V in zip(members, alone):
+        assert torch.equal(U, V)
+    b.close()
