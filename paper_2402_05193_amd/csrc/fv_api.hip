@@ -869,10 +869,13 @@ constexpr int MAX_GRAPHS = 16;   // cached step graphs per batch
 size_t align_up(size_t v) { return (v + TAB_ALIGN - 1) & ~(TAB_ALIGN - 1); }
 
 struct BatchGroup {
-    int gid, model, dtype, pos, rec, variant, count, nblocks;
+    int gid, model, dtype, pos, rec, variant, count, nblocks, solo_blocks;
     size_t hdr_off, first_off, args_off[3];  // byte offsets in the device table
-    // a group of one member runs the single-problem stage kernel with these arguments
-    // (the same body: the same results, without the table indirection)
+    // a group of one member runs the single-problem stage kernel with these arguments (the
+    // same body: the same results, without the table indirection) and the z chunks of a
+    // single problem, as it has the GPU to itself: against the chunks of batched members an
+    // Euler FP64 step 118 -> 64 us at 40^3, 538 -> 463 at 192x96x96; FP32 NS with limiters at
+    // 128^3, where the estimate is at its worst, 552 -> 574
     fv::StageArgs<double> solo_d[3];
     fv::StageArgs<float> solo_f[3];
 };
@@ -952,6 +955,21 @@ void fill_group_args(const fv_config* c, void* U, void* ws, char* img, const Bat
     *nblocks = geo.nblocks;
 }
 
+// the stage arguments of a group's only member from the table image, with the z chunks of a
+// single-problem launch; returns its workgroups
+template <typename Real>
+int solo_args(const fv_config* c, const char* img, const size_t* args_off, fv::StageArgs<Real>* out)
+{
+    fv::LaunchGeom geo;
+    const fv::StageArgs<Real> a = stage_args<Real>(c, geo, true);
+    for (int s = 0; s < 3; s++) {
+        out[s] = *reinterpret_cast<const fv::StageArgs<Real>*>(img + args_off[s]);
+        out[s].zchunk = a.zchunk;
+        out[s].nchunks = a.nchunks;
+    }
+    return geo.nblocks;
+}
+
 int batch_launch_steps(fv_batch* b, int nsteps, hipStream_t st, bool bucketed)
 {
     const fv::BatchScalars* scal = reinterpret_cast<const fv::BatchScalars*>(b->table + b->scal_off);
@@ -961,7 +979,7 @@ int batch_launch_steps(fv_batch* b, int nsteps, hipStream_t st, bool bucketed)
             for (const BatchGroup& g : b->groups) {
                 if (!bucketed && g.count == 1) {
                     fv::LaunchGeom geo;
-                    geo.nblocks = g.nblocks;
+                    geo.nblocks = g.solo_blocks;
                     hipError_t e = g.dtype == FV_F64 ? fv::launch_stage<double>(g.model, g.solo_d[s], geo, st)
                                                      : fv::launch_stage<float>(g.model, g.solo_f[s], geo, st);
                     if (e != hipSuccess) return hip_fail(e, "batch stage launch (single member)");
@@ -1115,12 +1133,13 @@ int batch_set(fv_batch* b, int32_t n, const fv_config* cfgs, void* const* U, voi
     }
     char* img = b->host[k];
     memset(img, 0, end);
-    std::vector<int> slot(groups.size(), 0), first(groups.size(), 0);
+    std::vector<int> slot(groups.size(), 0), first(groups.size(), 0), first_of(groups.size(), 0);
     bool starts = false;
     fv::BatchScalars* sc = reinterpret_cast<fv::BatchScalars*>(img + scal_off);
     for (int i = 0; i < n; i++) {
         const int p = pos_of[gid[i]];
         BatchGroup& g = groups[p];
+        if (slot[p] == 0) first_of[p] = i;
         int nb = 0;
         if (g.dtype == FV_F64) fill_group_args<double>(&cfgs[i], U[i], ws[i], img, g, slot[p], first[p], &nb);
         else fill_group_args<float>(&cfgs[i], U[i], ws[i], img, g, slot[p], first[p], &nb);
@@ -1138,12 +1157,11 @@ int batch_set(fv_batch* b, int32_t n, const fv_config* cfgs, void* const* U, voi
         reinterpret_cast<int*>(img + groups[p].hdr_off)[0] = groups[p].count;
         reinterpret_cast<int*>(img + groups[p].first_off)[groups[p].count] = first[p];
         groups[p].nblocks = first[p];
-        for (int s = 0; s < 3; s++) {
-            if (groups[p].dtype == FV_F64)
-                groups[p].solo_d[s] = reinterpret_cast<const fv::StageArgs<double>*>(img + groups[p].args_off[s])[0];
-            else
-                groups[p].solo_f[s] = reinterpret_cast<const fv::StageArgs<float>*>(img + groups[p].args_off[s])[0];
-        }
+        if (groups[p].count != 1) continue;
+        const fv_config* c = &cfgs[first_of[p]];
+        groups[p].solo_blocks = groups[p].dtype == FV_F64
+                                    ? solo_args<double>(c, img, groups[p].args_off, groups[p].solo_d)
+                                    : solo_args<float>(c, img, groups[p].args_off, groups[p].solo_f);
     }
     reinterpret_cast<int*>(img + scal_hdr_off)[0] = n;
     // kernel attributes before any capture

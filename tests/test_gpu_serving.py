@@ -318,3 +318,31 @@ def test_server_results_same_alone_and_in_the_mix(use_graph, fill, policy):
     assert srv.heap.available == srv.heap.size
     print("batched", st.summary(), "\nsequential", st2.summary(), flush=True)
     srv.close()
+
+
+def test_batch_of_one_takes_the_single_problem_chunks():
+    """A group of one member has the GPU to itself: its steps take the z chunks of a
+    single-problem launch.  Compared by time, with room for noise: the chunks of batched
+    members take 2.4 times as long on this grid."""
+    cfg = S.Config(nx=32, ny=32, nz=32, dx=0.1, dy=0.1, dz=0.1, model=S.EULER, cfl=1e-3)
+    W = 1.0 + 0.1 * torch.rand(cfg.shape, dtype=torch.float64, device="cuda")
+    U, ws = S.prim_to_cons(cfg, W, S.empty_state(cfg)), S.workspace(cfg)
+    V, wv = U.clone(), S.workspace(cfg)
+    b = S.Batch(1)
+    b.set([(cfg, V, wv)], fresh=[1])
+
+    def best(step):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(20):
+            e0.record()
+            step(10)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times)
+
+    alone = best(lambda n: S.advance(cfg, U, n, 0.0, ws))
+    batched = best(b.step)
+    b.close()
+    assert batched <= 1.5 * alone
