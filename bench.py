@@ -393,8 +393,8 @@ def main():
                     help="requests of the serving benchmark (0: skip it)")
     ap.add_argument("--serve-fill", type=int, default=768,
                     help="a request joins the running batch while the batch has fewer stage workgroups than "
-                         "this (0: whenever a slot and memory are free); 768 = the FP32 stage workgroups resident "
-                         "on 256 CUs at once")
+                         "this (0: whenever a slot and memory are free); 768 = three FP32 stage workgroups on each "
+                         "of 256 CUs")
     ap.add_argument("--serve-only", action="store_true", help="run the serving benchmark alone and print its JSON")
     ap.add_argument("--serve-eager", action="store_true", help="batched steps without graph replay")
     ap.add_argument("--serve-backlog", type=int, default=8,

@@ -175,9 +175,10 @@ int rhs(const fv_config* cfg, const void* U, void* R, double dt, void* stream);
 int rhs_ws(const fv_config* cfg, const void* U, void* R, double dt, void* ws, void* stream);
 
 /* Workgroups of the problem's share of a batched stage launch; a measure of how
- * much of the GPU the problem fills (each CU holds two FP64 or three FP32 stage
- * workgroups at a time).  A single-problem launch chooses its z chunks, and so its
- * number of workgroups, by itself (results do not depend on them). */
+ * much of the GPU the problem fills (each CU holds two FP64 stage workgroups at a
+ * time, in FP32 three, or four of the kernels that need few registers).  A
+ * single-problem launch, and a batch group of one member, choose their z chunks,
+ * and so their number of workgroups, by themselves (results do not depend on them). */
 int stage_workgroups(const fv_config* cfg, int32_t* out);
 
 /* Bytes of the limiter decision record of rhs_flags: one byte per cell face,
@@ -265,7 +266,8 @@ int advance_noalloc(const fv_config* cfg, void* U, int32_t nsteps, double dt, vo
 int rhs_adjoint(const fv_config* cfg, const void* U, const void* Rbar, void* Ubar, void* ws,
                 void* stream);
 
-/* Bytes of workspace for rk3_step_adjoint: five state arrays. */
+/* Bytes of workspace for rk3_step_adjoint: five state arrays (the sweep uses the
+ * first four; the size is kept for callers that stored it). */
 int adjoint_workspace_bytes(const fv_config* cfg, size_t* out);
 
 /* Reverse sweep of one TVD-RK3 step at a fixed dt (Sec. 3.4): on entry Ubar

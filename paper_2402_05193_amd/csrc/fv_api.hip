@@ -43,7 +43,7 @@ size_t state_bytes(const fv_config* c)
 // z chunks of batched members: a launch aims at FV_TARGET_WORKGROUPS workgroups (tile
 // columns x z chunks), FP64 and FP32 (its kernels hold fewer registers, more workgroups fit
 // a CU), with chunks of at least FV_MIN_ZCHUNK planes, unless the member alone would then
-// have fewer workgroups than the GPU holds at once (2 FP64 or 3 FP32 stage workgroups on
+// have fewer workgroups than the GPU holds at once (taken as 2 FP64 or 3 FP32 workgroups on
 // each of the 256 CUs); then halved down to FV_SMALLEST_ZCHUNK.  The other members fill the
 // GPU, so shorter chunks only repeat march starts: with chunks down to 2 or 1 planes a
 // batch of six requests took 2.97 / 3.08 against 2.91 ms.
@@ -185,14 +185,20 @@ bool positivity_on(const fv_config* c)
 // least estimated time, (planes + start) x the time per plane of a CU's fullest load.  A
 // chunk's start (window loads, z-only and warm-up steps) costs about one plane step, and
 // with n workgroups on a CU, of which S run at once, a plane step of each takes load[n]
-// times that of one alone; full rounds of S follow each other.  S: 2 in FP64, 3 in FP32, 4
-// for the FP32 single-phase primitive WENO5-Z kernels without limiters (116 VGPRs).  The
-// constants are fitted to stage times at 150 sizes from 200x1x1 to 256^3 of the three
-// models, each with chunks of 1 to 128 planes: the estimate's choice is within 0.1 % of the
-// fastest chunk on average in FP64, within 0.3 % and 2 % in FP32.  Against the rule that
-// batched members keep, ms per stage: Euler 32^3 0.037 -> 0.016, 64^3 0.041 -> 0.033, 128^3
-// 0.191 -> 0.172; NS 176^3 0.721 -> 0.658, 256^3 1.874 -> 1.832, FP32 128^3 0.186 -> 0.149;
-// five-equation 200^3 1.88 -> 1.56, 256^3 2.74 -> 2.60, FP32 192x96x96 0.226 -> 0.169.
+// times that of one alone; full rounds of S follow each other.  The constants were fitted to
+// stage times of the primitive WENO5-Z kernels from 200x1x1 to 256^3.  FP64 (S = 2, what
+// registers and LDS allow): measured at 19 such sizes with chunks of 1 to 128 planes, the
+// choice is within 0.1 % of the fastest chunk on average and 0.8 % at worst for every model
+// and family (limiters, characteristic, TENO6-A, THINC, external viscous fluxes).  FP32: S and
+// the longest chunks (8 and 11 planes) are constants of the fit, made before the arithmetic
+// of its reconstruction was last changed, not the kernels' residency: all single-phase
+// kernels of constant viscosity and the five-equation ones without limiters and THINC hold
+// at most 134 VGPRs, most of them 128 or fewer, so that four workgroups fit a CU.  The
+// choice is within 0.4 % of the fastest for the five-equation kernels with limiters and
+// 1.5-3.6 % for the others, at worst 16 % (80^3 and 101x75x53, where 2 planes are better).
+// Against the rule that batched members keep, us per stage: Euler 32^3 37 -> 15, 64^3 38 ->
+// 30, 128^3 equal; NS 176^3 714 -> 646, 256^3 1868 -> 1809, FP32 128^3 equal, 256^3 1114 ->
+// 1134; five-equation 200^3 1359 -> 1217, 256^3 2319 -> 2291, FP32 192x96x96 220 -> 185.
 // Results do not depend on the chunks.
 int solo_zchunk(const fv_config* c, long long tiles)
 {
@@ -761,7 +767,7 @@ int adjoint_workspace_bytes(const fv_config* cfg, size_t* out)
 // Reverse sweep of one TVD-RK3 step from its stage states U1, U2 (Sec. 3.4):
 // U1 = Un + dt R(Un); U2 = 3/4 Un + 1/4 U1 + 1/4 dt R(U1); U3 = 1/3 Un + 2/3 U2 + 2/3 dt R(U2).
 // On entry Ubar holds the cotangent of U3, on return that of Un.  aws holds G2 and G1 at
-// state slots 2 and 3 (slots 0 and 1 are free for the caller's stage states).
+// state slots 2 and 3 (slots 0 and 1 are free for the caller's stage states; slot 4 is unused).
 static int step_adjoint_sweep(const fv_config* cfg, const void* Un, const void* U1p, const void* U2p, void* Ubar,
                               double dt, void* aws, hipStream_t st)
 {

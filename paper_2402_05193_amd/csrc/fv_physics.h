@@ -277,11 +277,13 @@ __device__ __forceinline__ Real weno5z_value(Real v, Real d1, Real d2, Real d3, 
     return fma(n, rcp(fma(Real(3), g2, fma(Real(6), g1, g0))), v);
 }
 
-// The same values from the candidate polynomials themselves, for FP32: in 24 bits a change
-// of rounding shows wherever a result is compared more closely than its type resolves (the
-// time step of the fastest cell is handed out as a double), so the primitive FP32 kernels
-// keep this arithmetic.  The differences would be faster: NS 128^3 457 against 506 us per
-// step, THINC 192x96x96 653 against 705.
+// The same values from the candidate polynomials themselves, for the primitive FP32 kernels.
+// A user's FP32 runs stay bit for bit what they were, and with them the time step of
+// rk3_stage3_cfl, which is handed out as a double: in differences it moved by up to 1.2e-7
+// relative, an FP32 rounding, but more than a double result may move unnoticed.  The
+// differences are no less accurate (the characteristic and TENO6-A kernels use them in FP32
+// too: 15-24 % less RMS error against FP64 on average) and would be faster: NS 128^3 457
+// against 506 us per step, THINC 192x96x96 653 against 705.
 __device__ __forceinline__ void weno5z_pair_expanded(float a, float b, float c, float d, float e, float eps, float& vm,
                                                      float& vp)
 {

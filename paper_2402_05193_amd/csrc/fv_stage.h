@@ -417,9 +417,10 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
     for (int s = s_begin; s <= z1 + 1; s += one_z ? 2 : 1) {
         // the thread's indices formed anew in every step from a copy that the compiler does
         // not see through: otherwise it computes the index arithmetic of every phase once
-        // and holds it in registers across the plane loop.  NS FP64 56 -> 0 spilled VGPRs,
-        // FP32 16 -> 0 (168 -> 139 VGPRs), five-equation FP64 84 -> 70; per stage NS 256^3
-        // 2.40 -> 2.06 ms, five-equation THINC FP32 192x96x96 0.33 -> 0.30
+        // and holds it in registers across the plane loop.  NS FP64 46 -> 4 spilled VGPRs (64
+        // -> 14 with limiters), FP32 163 -> 116 VGPRs, five-equation FP64 48 -> 18 (THINC 132
+        // -> 103); per stage NS 256^3 2.06 -> 1.82 ms, FP32 1.29 -> 1.14, five-equation
+        // 256x128x128 0.657 -> 0.595, THINC FP32 192x96x96 0.246 -> 0.219; Euler equal
         int tid = threadIdx.x;
         pin(tid);
         const bool has_cell = tid < NCELL;
@@ -725,11 +726,13 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
                 for (int m = 0; m < NC; m++) vm_new[m] = vp[m] = Real(0);
             }
             // one component after the other where the registers are short of the interleaved
-            // form: five-equation FP64 (64 -> 18 spilled VGPRs, 2.08 -> 1.86 ms per step at
-            // 256x128x128) and THINC FP32 (0.688 -> 0.672 ms at 192x96x96), and where a fourth
-            // workgroup fits a CU (single phase FP32, 138 -> 116 VGPRs: NS 256^3 3.61 -> 3.22
-            // ms, Euler 2.27 -> 2.20).  Elsewhere it costs 1-3 % (NS FP64, the limited FP32
-            // kernels).
+            // form: five-equation FP64 (64 -> 18 spilled VGPRs, 0.664 -> 0.595 ms per stage at
+            // 256x128x128, THINC 1.215 -> 1.168).  The FP32 families were chosen with WENO5-Z
+            // in differences; with the candidate polynomials the order matters little there
+            // (single phase 118 against 116 VGPRs): in order, NS 256^3 takes 1.140 against
+            // 1.131 ms, Euler 0.858 against 0.848, THINC 192x96x96 0.219 against 0.214.
+            // Elsewhere it costs 1-2 % (NS 256^3 FP64 1.820 -> 1.850, limited FP32 NS 160^3
+            // 0.332 -> 0.337, five-equation 192x96x96 0.186 -> 0.189).
             constexpr bool Z_IN_ORDER =
                 sizeof(Real) == 8 ? MODEL == DIM : (THINC || (MODEL != DIM && POS == 0));
             if (!FACE && !one_z) {
@@ -887,8 +890,11 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             // the co-resident workgroup's waves, so that the workgroup reaches the barrier
             // sooner: the reconstruction phases' remainder waves priority 1, the face phases'
             // remainder wave priority 2.  NS 256^3 2.260 -> 2.18 ms per stage, five-equation
-            // 256x128x128 0.949 -> 0.914 ms, Euler equal; FP32 (three workgroups per CU)
-            // measured 0.4-2 % slower with it and keeps the default priority.
+            // 256x128x128 0.949 -> 0.914 ms, Euler equal.  FP32 keeps the default
+            // priority: it measured 0.4-2 % slower with the raised one when three workgroups
+            // fitted a CU; with the present kernels it would be faster but for limited NS (NS
+            // 256^3 1.140 -> 1.115 ms, 128^3 0.165 -> 0.151, five-equation 192x96x96 0.186 ->
+            // 0.178, limited NS 160^3 0.332 -> 0.342).
             constexpr int P1_ITEMS = CHARV ? TL::NFX : (TENO ? NC * TL::NFX : NC * (BX + 2) * BY / 2);
             constexpr int P4_ITEMS = CHARV ? TL::NFY : (TENO ? NC * TL::NFY : NC * BX * (BY + 2) / 2);
             const bool prio_p1 = sizeof(Real) == 8 && (rt >> 6) < ((P1_ITEMS % NT) + 63) / 64;
@@ -1218,8 +1224,9 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
             for (int f = 0; f < NC; f++) {
                 win[q][f] = win[q + 1][f];
                 // otherwise the compiler carries the differences that the next step's z
-                // reconstruction shares with this one's in registers (five-equation
-                // THINC FP64 133 -> 113 spilled VGPRs, 1016 -> 956 us per step at 160x80x80)
+                // reconstruction shares with this one's in registers; with the z work in
+                // order it hardly does (five-equation THINC FP64 103 spilled VGPRs either
+                // way, 1173 -> 1168 us per stage at 256x128x128; the others equal)
                 pin(win[q][f]);
             }
         if constexpr (THINC) {
@@ -1244,7 +1251,8 @@ __device__ __forceinline__ void stage_body(const StageArgs<Real>& a, const int b
 }
 
 // Waves per SIMD the stage kernels are compiled for: two in FP64 (256 registers per
-// lane), three in FP32 (168), where the narrower state leaves room for a third
+// lane), three in FP32 (168), where the narrower state leaves room for a third (and, in
+// kernels of at most 128 registers, a fourth)
 template <typename Real>
 constexpr int stage_waves()
 {
